@@ -200,7 +200,7 @@ nova_kv_status prepare_decode(const nova_kv_params *p, const nova_kv_layout *lay
   // every value format runs on the table kernels where their layout applies
   const bool sq = (p->flags & NOVA_KV_SQ_VALUES) != 0;
   plan = novakv::plan_decode(batch, num_q_heads, p->num_kv_heads, p->head_dim, max_seq_len, layout->block_size,
-                             window, false);
+                             window);
   if ((st = debug_check(layout, batch, seq_lens, max_seq_len, nullptr, need_encode ? 1 : 0, stream)) != NOVA_KV_OK)
     return st;
   if (static_ws) {  // the allocation-free step: the GPU's fixed scratch array (the last check)
@@ -248,12 +248,10 @@ nova_kv_status prepare_decode(const nova_kv_params *p, const nova_kv_layout *lay
   a.window = window;
   a.sinks = sinks;
   a.scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf(static_cast<float>(p->head_dim));
-  a.qscale = plan.use_lut ? a.scale * 1.44269504088896341f : a.scale;
+  a.qscale = a.scale * 1.44269504088896341f;
   a.out = out;
   char *ws = static_cast<char *>(workspace);
   a.counters = reinterpret_cast<int *>(ws + plan.off_cnt);
-  a.qp = reinterpret_cast<float *>(ws + plan.off_qp);
-  a.sinkp = reinterpret_cast<float *>(ws + plan.off_sinkp);
   a.part_ml = reinterpret_cast<float *>(ws + plan.off_ml);
   a.part_acc = reinterpret_cast<float *>(ws + plan.off_acc);
   a.newp = reinterpret_cast<float *>(ws + plan.off_new);

@@ -55,14 +55,13 @@ struct DecodeArgs {
   int max_seq_len, window;
   const float *sinks;
   float scale;      // softmax scale (natural-log units)
-  float qscale;     // factor folded into q' (scale, or scale * log2(e) for the table path)
+  float qscale;     // factor folded into q': scale * log2(e)
   float *out;
   // workspace carve-out
   int *counters;    // [B][Hkv]       split arrival counters (zero between calls)
-  float *qp;        // [B][Hq][D]     pre-transformed, pre-scaled queries
-  float *sinkp;     // [B][Hq]        shifted sink logits (-inf when no sink)
   float *part_ml;   // [B][Hq][n_split][2]  running max, denominator
-  float *part_acc;  // [B][Hq][n_split][D]  transform-domain value accumulator
+  float *part_acc;  // [B][Hq][n_split][D]  transform-domain value accumulator (decode_vq: a second
+                    // block of the same shape holds the band's value sums)
   int n_split;      // context splits per sequence
   int chunk;        // tokens per split
   int b_chunk;      // table kernels: sequences per block of the workgroup order (divides batch)
@@ -146,17 +145,17 @@ __host__ __device__ __forceinline__ AttendedSpans attended_spans(int lo, int S, 
 
 // Split plan and workspace carve-out of the decode path.
 struct DecodePlan {
-  int use_lut;      // 1: table-based stage 1 (decode_lut.hip), 0: generic stage 1
+  int use_lut;      // 1: table kernels (decode_lut.hip, decode_lut64.hip), 0: decode_vq.hip
   int n_split;
   int chunk;
-  size_t off_cnt, off_qp, off_sinkp, off_ml, off_acc, off_new, off_xch, off_xnew, off_xgrp, total;
+  size_t off_cnt, off_ml, off_acc, off_new, off_xch, off_xnew, off_xgrp, total;
 };
 // Splits tile each sequence's attended span (the last `window` tokens, or all).
 // The workspace (off_*, total) is sized for every window and both decode
 // paths, so it depends only on (batch, heads, head_dim, max_seq_len);
 // block_size <= 0 asks for that size alone.
 DecodePlan plan_decode(int batch, int num_q_heads, int num_kv_heads, int head_dim,
-                       int max_seq_len, int block_size, int window, bool split_k_only = false);
+                       int max_seq_len, int block_size, int window);
 
 hipError_t launch_decode(const DecodeArgs &a, int use_lut, hipStream_t stream);
 int plan_b_chunk(int batch, int num_kv_heads, int n_split);
@@ -170,6 +169,8 @@ bool lut_path_eligible(int head_dim, int gqa, int block_size);
 void plan_lut(int batch, int num_kv_heads, int max_seq_len, int *n_split, int *chunk);
 hipError_t launch_decode_lut(const DecodeArgs &a, hipStream_t stream);    // head_dim 128
 hipError_t launch_decode_lut64(const DecodeArgs &a, hipStream_t stream);  // head_dim 64
+// Everything else: up to kMaxGqa query heads per KV head, any block size.
+hipError_t launch_decode_vq(const DecodeArgs &a, hipStream_t stream);
 hipError_t launch_encode(const EncodeArgs &a, hipStream_t stream);
 
 __device__ __forceinline__ float half_bits_to_float(uint16_t h) {
