@@ -93,8 +93,11 @@ __device__ __forceinline__ float input_value(const void *p, const size_t i, cons
   return bf16 ? bf16_bits_to_float(static_cast<const uint16_t *>(p)[i]) : static_cast<const float *>(p)[i];
 }
 
-// hi and lo parts of an fp32 value (|x| below the fp16 range)
-__device__ __forceinline__ void split_f16(const float x, _Float16 &hi, _Float16 &lo) {
+// hi and lo parts of an fp32 value (|x| below the fp16 range).  x is made
+// opaque: a product fused into one of the conversions of hi but not the other
+// would leave two different roundings of it.
+__device__ __forceinline__ void split_f16(float x, _Float16 &hi, _Float16 &lo) {
+  asm volatile("" : "+v"(x));
   hi = static_cast<_Float16>(x);
   lo = static_cast<_Float16>((x - static_cast<float>(hi)) * kLoUp);
 }
