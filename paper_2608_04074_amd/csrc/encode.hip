@@ -28,6 +28,20 @@ __device__ __forceinline__ void store_band(const EncodeArgs &a, const int side, 
       bits;
 }
 
+// The same for elements d .. d + 3 (d a multiple of 4), given as fp32 bits (of
+// bf16 values, or fp32 ones, rounded to nearest even).
+__device__ __forceinline__ void store_band4(const EncodeArgs &a, const int side, const int b, const int kv,
+                                            const int pos, const int end, const int d, const uint4 x) {
+  uint16_t *band = side == 0 ? a.band_k : a.band_v;
+  if (!band || !position_in_pool(a.layout, pos)) return;
+  if (!(pos < a.n_sink || (a.n_rec > 0 && pos >= end - a.n_rec))) return;
+  const int nb = a.n_sink + a.n_rec;
+  auto bits = [](const uint32_t f) { return (f + 0x7fffu + ((f >> 16) & 1u)) >> 16; };
+  *reinterpret_cast<uint2 *>(
+      band + ((static_cast<size_t>(b) * a.num_kv_heads + kv) * nb + band_slot(pos, a.n_sink, a.n_rec)) * a.head_dim + d) =
+      make_uint2(bits(x.x) | (bits(x.y) << 16), bits(x.z) | (bits(x.w) << 16));
+}
+
 // bf16 bits of an input element: as stored, or an fp32 value rounded to
 // nearest even.
 __device__ __forceinline__ uint16_t input_bf16_bits(const EncodeArgs &a, const void *src, const size_t idx) {
@@ -104,8 +118,8 @@ __device__ __forceinline__ double wave_max(double x) {
   return fmax(x, y);
 }
 
-// Few new tokens per sequence (a decode step): one workgroup per (token,
-// sequence, KV head, side, block of 8 groups).  A block needs 32 transform
+// Few new tokens (a decode step of a few sequences), plain formats: one workgroup
+// per (token, sequence, KV head, side, block of 8 groups).  A block needs 32 transform
 // columns (D x 32 fp32) and its 8 codebooks (16 KB), so each workgroup
 // fetches a quarter (D=128) or half (D=64) of the parameters, all loads
 // coalesced and issued before the first use; the launch costs about one
@@ -117,7 +131,6 @@ __global__ void __launch_bounds__(256) encode_small(EncodeArgs a) {
   __shared__ encblk::Scratch<D> sc;
   const int blk = blockIdx.x % NB;
   const int side = (blockIdx.x / NB) & 1;
-  if (side == 1 && a.v_sq) return;  // the scalar value arm has its own kernel
   const int t = blockIdx.x / (2 * NB);
   const int kv = blockIdx.y, b = blockIdx.z;
   const int tid = threadIdx.x;
@@ -145,33 +158,9 @@ __global__ void __launch_bounds__(256) encode_small(EncodeArgs a) {
   }
   __syncthreads();
   const size_t off = code_row_offset(a.layout, a.num_kv_heads, L, b, kv, pos);
-  int code;
-  if (side == 0 && a.k_scales) {
-    // Key-scale format: rho needs every coefficient of the key, so the
-    // workgroup forms all NB blocks' coefficients (the same computation as
-    // the block's own), keeps them in LDS, and searches its block with the
-    // coefficients divided by rho; block 0's workgroup stores rho.
-    __shared__ double us[D];
-    __shared__ double srho;
-    T4 tb[D / 32];
-    encblk::load_rows<D>(tid, tm, TBF, 0, tb);
-    encblk::token_coefficients<D>(tid, sc, tm, TBF, tb, us, [] { __syncthreads(); });
-    if (tid == 0) srho = encblk::key_scale<D>(us);
-    __syncthreads();
-    const double rho = srho;
-    double uu[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const double u = us[encblk::kCols * blk + 4 * (tid >> 5) + i];
-      uu[i] = rho > 0.0 ? u / rho : 0.0;
-    }
-    code = encblk::search_codes(tid, uu, cw, FP8);
-    if (blk == 0 && tid == 0) a.k_scales[off / L] = encblk::bf16_of(rho);
-  } else {
-    encblk::partial_block<D>(tid, sc, trow, TBF);
-    __syncthreads();
-    code = encblk::search_block<D>(tid, sc, cw, FP8);
-  }
+  encblk::partial_block<D>(tid, sc, trow, TBF);
+  __syncthreads();
+  const int code = encblk::search_block<D>(tid, sc, cw, FP8);
   if ((tid & 31) == 0) pool[off + encblk::kGroups * blk + (tid >> 5)] = static_cast<uint8_t>(code);
 }
 
@@ -211,8 +200,9 @@ __global__ void __launch_bounds__(256) encode_small(EncodeArgs a) {
 // the block minima, about 12 for operands, the block's 8 scores and the rest.
 // (All scores in fp64 took 64 for the products and 48 for the argmin.)
 // 4096 tokens of 32 sequences, 8 KV heads of 128: 4309 us with fp64 scores, 2352
-// us now; 2 x 6001 tokens of head_dim 64 in the deployed format: 436 us (321 of
-// them a workgroup per token for the scalar arm), now 96 us.
+// us like this, 2111 with the inputs loaded all at once (one element and one
+// wait at a time before); 2 x 6001 tokens of head_dim 64 in the deployed format:
+// 436 us (321 of them a workgroup per token for the scalar arm), 96, now 72 us.
 constexpr int kTileWaves = 8;
 constexpr int kSelPart = 8192;  // LDS bytes before the search's staging, for the per-token reductions
 
@@ -224,7 +214,13 @@ struct TileShape {
   static constexpr int RS = D + 2;                   // LDS row stride of the inputs (doubles)
   static constexpr int BYTES_IN = TOKENS * RS * 8;
   static constexpr int BYTES_SEARCH = kSelPart + kTileWaves * 4096;
-  static constexpr int BYTES = BYTES_IN > BYTES_SEARCH ? BYTES_IN : BYTES_SEARCH;
+  // a quarter's transform (below): its coefficients, one copy per half of the
+  // contraction, past the search's staging
+  static constexpr int CT = OT / 4, RQ = 16 * CT + 2;
+  static constexpr int BYTES_QUARTER = BYTES_SEARCH + 2 * TOKENS * RQ * 8;
+  static constexpr int bytes(const bool split) {
+    return split ? (BYTES_IN > BYTES_QUARTER ? BYTES_IN : BYTES_QUARTER) : (BYTES_IN > BYTES_SEARCH ? BYTES_IN : BYTES_SEARCH);
+  }
 };
 
 typedef double double4_t __attribute__((ext_vector_type(4)));
@@ -305,14 +301,18 @@ __device__ int search_exact(const void *cb, const size_t cw, const int lane, con
   return arg;
 }
 
-// NTT: 16-token tiles per wave (1, 2 or 4).  SPLIT: a workgroup searches one of
-// the four groups of each wave (blockIdx.z >> 1 says which) instead of all
-// four, for launches whose tiles alone leave the chip idle.
+// NTT: 16-token tiles per wave (2 or 4).  SPLIT: a workgroup searches a quarter
+// of the groups (blockIdx.z >> 1 says which), one per wave, for launches whose
+// tiles alone leave the chip idle.  It forms only the quarter's coefficients:
+// four 16 x 16 tiles, the contraction in two halves, one per wave, added in LDS.
+// A scaled key needs them all: there every workgroup runs the whole transform
+// and wave ot searches group 4 ot + quarter.
 template <int D, bool FP8, bool TBF, int NTT, bool SPLIT>
 __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
   using T_ = TileShape<D, NTT>;
   constexpr int L = D / kGroupDim, NT = 64 * kTileWaves, TOK = T_::TOKENS, RS = T_::RS, KS = D / 4;
-  __shared__ __attribute__((aligned(16))) uint8_t smem[T_::BYTES];
+  constexpr int BYTES = T_::bytes(SPLIT);
+  __shared__ __attribute__((aligned(16))) uint8_t smem[BYTES];
   double *xs = reinterpret_cast<double *>(smem);
 
   const int kv = blockIdx.y, side = blockIdx.z & 1;
@@ -333,58 +333,107 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
   // inputs are staged: rows 4 ks + q, column 16 ot + m of T
   const int m = lane & 15, q = lane >> 4;
   const int ot = wave % T_::OT, th = wave / T_::OT;
+  const bool quarter = SPLIT && !scalar_arm && !(side == 0 && a.k_scales);
+  // a quarter's transform: wave = (half of the contraction, token tile, coefficient tile)
+  const int qc = wave % T_::CT, qt = (wave & 3) / T_::CT, qh = wave >> 2;
   uint32_t tr[KS];  // as loaded (fp32 words, or zero-extended bf16)
+  if (quarter) {
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) tr[ks] = load_t1_raw(tm, (4 * ks + q) * D + 16 * ot + m, TBF);
+    for (int ks = 0; ks < KS / 2; ++ks)
+      tr[ks] = load_t1_raw(tm, (4 * (ks + KS / 2 * qh) + q) * D + 16 * (T_::CT * only + qc) + m, TBF);
+  } else {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) tr[ks] = load_t1_raw(tm, (4 * ks + q) * D + 16 * ot + m, TBF);
+  }
 
-  // inputs (minus k_bar for keys) to LDS in fp64: thread tid stages
-  // coordinate tid mod D of tokens tid / D + k * (NT / D)
-  static_assert(NT % D == 0, "a thread stages one coordinate");
+  // the token that this lane stores: its position is requested here, its cache
+  // block after the barrier, so that neither is waited for where it is used
+  const int tok = 16 * NTT * th + lane;  // of the tile
+  bool stored = lane < 16 * NTT && n0 + tok < n_tok;
+  const int tok_b = stored ? (n0 + tok) / a.n_new : 0, tok_t = n0 + tok - tok_b * a.n_new;
+  const int tok_p0 = a.start_pos[tok_b];
+
+  // inputs (minus k_bar for keys) to LDS in fp64: thread tid stages four
+  // coordinates of tokens tid / (D / 4) + k * TP.  Every load is issued before
+  // the first is used: 8- or 16-byte loads where the inputs' address allows
+  // them, single elements otherwise.
   {
-    constexpr int TP = NT / D, NK = TOK / TP;
-    const int d = tid % D, s0 = tid / D;
-    const double kb = side == 0 ? static_cast<double>(a.kbar[kv * D + d]) : 0.0;
-    double x[NK];
+    constexpr int C4 = D / 4, TP = NT / C4, NK = TOK / TP;
+    static_assert(NT % C4 == 0 && TOK % TP == 0, "a thread stages four coordinates of NK tokens");
+    const int d = 4 * (tid % C4), s0 = tid / C4;
+    const float4 kb = side == 0 ? *reinterpret_cast<const float4 *>(a.kbar + kv * D + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+    uint4 x[NK];  // fp32 bits
+    auto index = [&](const int k) {  // past the last token the last one is read again
+      return (static_cast<size_t>(min(n0 + s0 + k * TP, n_tok - 1)) * a.num_kv_heads + kv) * D + d;
+    };
+    if (a.in_bf16) {
+      const uint16_t *p = static_cast<const uint16_t *>(src);
+      uint2 h[NK];
+      if (a.in_vec) {
 #pragma unroll
-    for (int k = 0; k < NK; ++k) {
-      const int i = n0 + s0 + k * TP;
-      x[k] = 0.0;
-      if (i < n_tok) {
-        const size_t idx = (static_cast<size_t>(i) * a.num_kv_heads + kv) * D + d;
-        x[k] = (a.in_bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(src)[idx]))
-                          : static_cast<double>(static_cast<const float *>(src)[idx])) - kb;
+        for (int k = 0; k < NK; ++k) h[k] = *reinterpret_cast<const uint2 *>(p + index(k));
+      } else {
+        uint16_t e[NK][4];
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) e[k][i] = p[index(k) + i];
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+          h[k] = make_uint2(e[k][0] | (static_cast<uint32_t>(e[k][1]) << 16), e[k][2] | (static_cast<uint32_t>(e[k][3]) << 16));
+      }
+#pragma unroll
+      for (int k = 0; k < NK; ++k)
+        x[k] = make_uint4(h[k].x << 16, h[k].x & 0xffff0000u, h[k].y << 16, h[k].y & 0xffff0000u);
+    } else if (a.in_vec) {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) x[k] = *reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(src) + index(k));
+    } else {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        const uint32_t *p = static_cast<const uint32_t *>(src) + index(k);
+        x[k] = make_uint4(p[0], p[1], p[2], p[3]);
       }
     }
 #pragma unroll
-    for (int k = 0; k < NK; ++k) xs[(s0 + k * TP) * RS + d] = x[k];
+    for (int k = 0; k < NK; ++k) {
+      double *row = xs + (s0 + k * TP) * RS + d;
+      const bool in = n0 + s0 + k * TP < n_tok;
+      const double2 lo = {static_cast<double>(__uint_as_float(x[k].x)) - static_cast<double>(kb.x),
+                          static_cast<double>(__uint_as_float(x[k].y)) - static_cast<double>(kb.y)};
+      const double2 hi = {static_cast<double>(__uint_as_float(x[k].z)) - static_cast<double>(kb.z),
+                          static_cast<double>(__uint_as_float(x[k].w)) - static_cast<double>(kb.w)};
+      *reinterpret_cast<double2 *>(row) = in ? lo : double2{0.0, 0.0};
+      *reinterpret_cast<double2 *>(row + 2) = in ? hi : double2{0.0, 0.0};
+    }
     if (a.band_k && (!SPLIT || only == 0)) {
       for (int k = 0; k < NK; ++k) {
         const int i = n0 + s0 + k * TP;
         if (i < n_tok) {
           const int b = i / a.n_new, t = i - b * a.n_new;
           const int p0 = a.start_pos[b] + a.start_offset;
-          store_band(a, side, b, kv, p0 + t, p0 + a.n_new, d,
-                     input_bf16_bits(a, src, (static_cast<size_t>(i) * a.num_kv_heads + kv) * D + d));
+          store_band4(a, side, b, kv, p0 + t, p0 + a.n_new, d, x[k]);
         }
       }
     }
   }
-  // the token that this lane stores, and its code row
-  const int tok = 16 * NTT * th + lane;  // of the tile
-  bool stored = lane < 16 * NTT && n0 + tok < n_tok;
-  size_t off = 0;
-  if (stored) {
-    const int i = n0 + tok, b = i / a.n_new, t = i - b * a.n_new;
-    const int pos = a.start_pos[b] + a.start_offset + t;
-    stored = position_in_pool(a.layout, pos);
-    if (stored) off = code_row_offset(a.layout, a.num_kv_heads, L, b, kv, pos);
-  }
   __syncthreads();
+  // the stored token's cache block, requested before the transform
+  const int tok_pos = tok_p0 + a.start_offset + tok_t;
+  stored = stored && position_in_pool(a.layout, tok_pos);
+  const int tok_blk = stored ? tok_pos / a.layout.block_size : 0;
+  int tok_phys = tok_b * a.layout.blocks_per_seq + tok_blk;
+  if (a.layout.block_table) tok_phys = a.layout.block_table[tok_phys];
 
   double4_t acc[NTT];
 #pragma unroll
   for (int j = 0; j < NTT; ++j) acc[j] = double4_t{0.0, 0.0, 0.0, 0.0};
-  {
+  if (quarter) {
+    const double *xr = xs + (16 * qt + m) * RS + q + 4 * (KS / 2) * qh;
+#pragma unroll
+    for (int ks = 0; ks < KS / 2; ++ks)
+      acc[0] = __builtin_amdgcn_mfma_f64_16x16x4f64(static_cast<double>(t1_raw_value(tr[ks], TBF)), xr[4 * ks], acc[0], 0, 0, 0);
+  } else {
     const double *xr = xs + (16 * NTT * th + m) * RS + q;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
@@ -395,6 +444,15 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
     }
   }
   __syncthreads();  // every wave has read its inputs; the region is free
+  double *quad = reinterpret_cast<double *>(smem + T_::BYTES_SEARCH);  // [2][TOK][RQ]
+  if (quarter) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) quad[(qh * TOK + 16 * qt + m) * T_::RQ + 16 * qc + 4 * k + q] = acc[0][k];
+    __syncthreads();
+  }
+  // the stored token's code row
+  const size_t off = ((static_cast<size_t>(tok_phys) * a.num_kv_heads + kv) * a.layout.block_size +
+                      (tok_pos - tok_blk * a.layout.block_size)) * L;
 
   if (scalar_arm) {
     // Scalar value arm (paper: Sec. "Bit rate" and the implementation table):
@@ -421,7 +479,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
         red[(T_::OT + ot) * TOK + 16 * NTT * th + 16 * j + m] = mx;
       }
     }
-    static_assert(2 * T_::OT * TOK * 8 <= T_::BYTES, "the reductions fit");
+    static_assert(2 * T_::OT * TOK * 8 <= BYTES, "the reductions fit");
     __syncthreads();
     uint32_t mine = 0u;  // the four code bytes of token `lane`
 #pragma unroll
@@ -509,24 +567,31 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
   const int row_cw = 16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3);
   const uint8_t *arow = stage + 2048 * half + 8 * row_cw;
   uint2 rn[4];  // codewords 4 lane .. 4 lane + 3 of the next group, as loaded
-  const int k_first = SPLIT ? only : 0, k_last = SPLIT ? only : 3;
-  auto group_cw = [&](const int k) { return cw0 + static_cast<size_t>(4 * ot + k) * kCodebookSize; };
+  const int g0 = !SPLIT ? 4 * ot : (quarter ? T_::OT * only + ot : 4 * ot + only);  // the wave's first group
+  auto group_cw = [&](const int k) { return cw0 + static_cast<size_t>(g0 + k) * kCodebookSize; };
 #pragma unroll
-  for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k_first) + 4 * lane + j);
+  for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(0) + 4 * lane + j);
   uint32_t code_acc = 0u;
 #pragma unroll
-  for (int kk = 0; kk < (SPLIT ? 1 : 4); ++kk) {
-    const int k = SPLIT ? only : kk;
+  for (int k = 0; k < (SPLIT ? 1 : 4); ++k) {
     // token side first: coordinate rows to lane = token
     double u[4] = {0.0, 0.0, 0.0, 0.0};
+    if (quarter) {
+      if (lane < 16 * NTT) {
+        const double *ur = quad + tok * T_::RQ + 4 * ot;
 #pragma unroll
-    for (int j = 0; j < NTT; ++j) {
-      if constexpr (SPLIT)
-        u[j] = only == 0 ? acc[j][0] : (only == 1 ? acc[j][1] : (only == 2 ? acc[j][2] : acc[j][3]));
-      else
-        u[j] = acc[j][kk];
+        for (int i = 0; i < 4; ++i) u[i] = ur[i] + ur[TOK * T_::RQ + i];
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NTT; ++j) {
+        if constexpr (SPLIT)
+          u[j] = only == 0 ? acc[j][0] : (only == 1 ? acc[j][1] : (only == 2 ? acc[j][2] : acc[j][3]));
+        else
+          u[j] = acc[j][k];
+      }
+      transpose_rows(u);  // u[i]: coordinate i of token `lane`
     }
-    transpose_rows(u);  // u[i]: coordinate i of token `lane`
 
     // codewords: the group's scale, its scaled codewords and norms into LDS
     uint2 w[4];
@@ -538,9 +603,9 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
       const u16x2 ax = __builtin_bit_cast(u16x2, w[j].x & 0x7fff7fffu), ay = __builtin_bit_cast(u16x2, w[j].y & 0x7fff7fffu);
       big = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, big), __builtin_elementwise_max(ax, ay)));
     }
-    if (kk + 1 < (SPLIT ? 1 : 4)) {
+    if (k + 1 < (SPLIT ? 1 : 4)) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(min(k + 1, k_last)) + 4 * lane + j);
+      for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
     }
     big = wave_max_u32(max(big & 0xffffu, big >> 16));
     // exponent of the largest coordinate (fp16 bits; denormals count as 2^-24 ..)
@@ -692,55 +757,18 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
   }
   if (stored) {
     if constexpr (SPLIT)
-      pool[off + 4 * ot + only] = static_cast<uint8_t>(code_acc);
+      pool[off + g0] = static_cast<uint8_t>(code_acc);
     else
-      *reinterpret_cast<uint32_t *>(pool + off + 4 * ot) = code_acc;
-  }
-}
-
-// Scalar value arm (paper: Sec. "Bit rate" and the implementation table:
-// per-token affine INT2 values with a BF16 scale and offset): one workgroup
-// (the 256-thread team of encode_block.h) per (new token, KV head,
-// sequence).  s = v t_v in fp64 with the block encoder's arithmetic, then
-// encode_block.h's levels; coordinate 4g + j goes to bits 2j, 2j + 1 of
-// byte g.  The token's value row also goes to the band when it is in it.
-template <int D, bool TBF>
-__global__ void __launch_bounds__(256) encode_sq_values(EncodeArgs a) {
-  constexpr int L = D / kGroupDim;
-  __shared__ encblk::Scratch<D> sc;
-  __shared__ double us[D];
-  __shared__ double red[2 * D / 64];
-  __shared__ uint8_t qs[D];
-  const int t = blockIdx.x, kv = blockIdx.y, b = blockIdx.z, i = threadIdx.x;
-  const int p0 = a.start_pos[b] + a.start_offset;
-  if (!position_in_pool(a.layout, p0 + t)) return;  // uniform: the workgroup stores nothing
-  const void *tv = transform_of(a.t_v, kv, D, TBF);
-  T4 rows[D / 32];
-  encblk::load_rows<D>(i, tv, TBF, 0, rows);
-  if (i < D) {
-    const size_t idx = ((static_cast<size_t>(b) * a.n_new + t) * a.num_kv_heads + kv) * D + i;
-    sc.xs[i] = a.in_bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(a.v)[idx]))
-                         : static_cast<double>(static_cast<const float *>(a.v)[idx]);
-    if (a.band_v) store_band(a, 1, b, kv, p0 + t, p0 + a.n_new, i, input_bf16_bits(a, a.v, idx));
-  }
-  __syncthreads();
-  auto sync = [] { __syncthreads(); };
-  encblk::token_coefficients<D>(i, sc, tv, TBF, rows, us, sync);
-  uint16_t sb, zb;
-  encblk::sq_levels<D>(i, us, red, qs, sync, sb, zb);
-  const size_t off = code_row_offset(a.layout, a.num_kv_heads, L, b, kv, p0 + t);
-  if (i < L) a.v_codes[off + i] = encblk::sq_byte(qs, i);
-  if (i == 0) {
-    a.v_sq[(off / L) * 2] = sb;
-    a.v_sq[(off / L) * 2 + 1] = zb;
+      *reinterpret_cast<uint32_t *>(pool + off + g0) = code_acc;
   }
 }
 
 // TBF: the transforms are stored as bf16 (a compile-time choice, so that the
 // fp32 kernels carry no branch on it).
 // Whole groups per wave once the tiles give every CU a workgroup; below that one
-// group per wave and tiles of half the tokens, four times the workgroups: 8
-// sequences of 24 tokens, 8 KV heads of 128, 38.7 us in 64-token tiles, 19.3 us.
+// group per wave and tiles of half the tokens, eight times the workgroups: 8
+// sequences of 24 tokens, 8 KV heads of 128, took 38.7 us in 64-token tiles,
+// 18.4 us so with the whole transform in each, 12.9 us with a quarter each.
 template <int D, bool FP8, bool TBF>
 void launch_tiles(const EncodeArgs &a, hipStream_t stream) {
   const long long n = static_cast<long long>(a.batch) * a.n_new;
@@ -753,11 +781,17 @@ void launch_tiles(const EncodeArgs &a, hipStream_t stream) {
         <<<dim3(blocks(TileShape<D, 2>::TOKENS), a.num_kv_heads, 8), dim3(64 * kTileWaves), 0, stream>>>(a);
 }
 
+// Few tokens in the plain formats: encode_small, a workgroup per token, side and
+// eight groups, as long as its workgroups stay below about six per CU (8 KV
+// heads of 128, one token per sequence: 7.8 us against 10.1 us in tiles for 16
+// sequences, 12.6 against 10.6 for 32).  The key scale and the scalar arm need
+// a token's whole transform, which the tiles form once (one sequence, both
+// formats: 10.8 us against 13.8 with a workgroup per token and block).
 template <int D, bool TBF>
 hipError_t launch_encode_t(const EncodeArgs &a, hipStream_t stream) {
-  if (a.n_new <= 4) {
-    if (a.v_sq) encode_sq_values<D, TBF><<<dim3(a.n_new, a.num_kv_heads, a.batch), dim3(256), 0, stream>>>(a);
-    const dim3 grid(2 * a.n_new * (D / kGroupDim / 8), a.num_kv_heads, a.batch);
+  const long long blocks = 2ll * (D / kGroupDim / encblk::kGroups) * a.n_new;
+  if (!a.k_scales && !a.v_sq && blocks * a.batch * a.num_kv_heads <= 1536) {
+    const dim3 grid(static_cast<unsigned>(blocks), a.num_kv_heads, a.batch);
     if (a.cb_fp8)
       encode_small<D, true, TBF><<<grid, dim3(256), 0, stream>>>(a);
     else
@@ -775,7 +809,10 @@ hipError_t launch_encode_d(const EncodeArgs &a, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t launch_encode(const EncodeArgs &a, hipStream_t stream) {
+hipError_t launch_encode(const EncodeArgs &args, hipStream_t stream) {
+  EncodeArgs a = args;
+  const uintptr_t addr = reinterpret_cast<uintptr_t>(a.k) | reinterpret_cast<uintptr_t>(a.v);
+  a.in_vec = addr % (a.in_bf16 ? 8 : 16) == 0 ? 1 : 0;
   switch (a.head_dim) {
     case 64: return launch_encode_d<64>(a, stream);
     case 128: return launch_encode_d<128>(a, stream);

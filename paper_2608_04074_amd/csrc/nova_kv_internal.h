@@ -111,6 +111,7 @@ struct EncodeArgs {
   CacheLayout layout;
   const void *k, *v;
   int in_bf16;
+  int in_vec;  // k and v start at a multiple of four elements' bytes (set by launch_encode)
   const int32_t *start_pos;
   int start_offset;  // the first new token of sequence b goes to start_pos[b] + start_offset
   uint8_t *k_codes, *v_codes;
