@@ -300,17 +300,18 @@ nova_kv_status nova_kv_decode_attn(const nova_kv_params *p, const nova_kv_layout
  *
  * out equals the output of nova_kv_decode_attn over the pools after that
  * append, up to fp32 rounding.  On 16-aligned blocks the step is a single
- * kernel launch, in which the workgroups that read the pools also encode the
- * new token and store what nova_kv_encode would:
+ * kernel launch where the plan finds that cheapest, and it then stores what
+ * nova_kv_encode would:
  *   - any format (key scale, scalar value arm, fp8) with a band whose n_rec
- *     >= 1, at head_dim 64, and at head_dim 128 on a contiguous cache or when
- *     the planner splits each (sequence, KV head) over more than one
- *     workgroup: the new token is the band's last row, stored in the launch
- *     and attended exactly from it, as the decode after the encode would;
- *   - head_dim 128, plain or fp8 codebooks, no band, when the planner splits
- *     each (sequence, KV head) over more than one workgroup: the new token
- *     is attended from its codes (its term is added after the split combine
- *     instead of inside a split).
+ *     >= 1: the workgroups that read the pools also encode the new token; it
+ *     is the band's last row, stored in the launch and attended exactly from
+ *     it, as the decode after the encode would;
+ *   - any format without a band, when the launch leaves CUs idle: workgroups of
+ *     their own encode the new token and hand its codes to the split that
+ *     holds its position, which attends it from them;
+ *   - head_dim 128, plain or fp8 codebooks, no band, over several splits per
+ *     (sequence, KV head): the workgroups that read the pools encode between
+ *     them, and the token's term is added after the split combine.
  * Otherwise the one-token encode and the decode run one after the other on
  * the stream.
  * batch == 0 is a valid no-op.

@@ -197,10 +197,12 @@ nova_kv_status prepare_decode(const nova_kv_params *p, const nova_kv_layout *lay
     return fail(NOVA_KV_ERR_INVALID_ARG, "q, k_codes, v_codes, seq_lens or out is NULL");
   if (!aligned(k_codes, 16) || !aligned(v_codes, 16))
     return fail(NOVA_KV_ERR_INVALID_ARG, "code pools must be 16-byte aligned");
-  // every value format runs on the table kernels where their layout applies
-  const bool sq = (p->flags & NOVA_KV_SQ_VALUES) != 0;
+  const bool sq = (p->flags & NOVA_KV_SQ_VALUES) != 0, key_scale = (p->flags & NOVA_KV_KEY_SCALE) != 0;
+  const int blocks = p->head_dim / 32;  // encoder tasks of one side
+  const novakv::StepFormat step{sq || key_scale, !band, band && band->n_rec >= 1, layout->block_table != nullptr,
+                                (key_scale ? 1 : blocks) + (sq ? 1 : blocks)};
   plan = novakv::plan_decode(batch, num_q_heads, p->num_kv_heads, p->head_dim, max_seq_len, layout->block_size,
-                             window);
+                             window, band ? band->n_sink + band->n_rec : 0, need_encode ? &step : nullptr);
   if ((st = debug_check(layout, batch, seq_lens, max_seq_len, nullptr, need_encode ? 1 : 0, stream)) != NOVA_KV_OK)
     return st;
   if (static_ws) {  // the allocation-free step: the GPU's fixed scratch array (the last check)
@@ -254,7 +256,6 @@ nova_kv_status prepare_decode(const nova_kv_params *p, const nova_kv_layout *lay
   a.counters = reinterpret_cast<int *>(ws + plan.off_cnt);
   a.part_ml = reinterpret_cast<float *>(ws + plan.off_ml);
   a.part_acc = reinterpret_cast<float *>(ws + plan.off_acc);
-  a.newp = reinterpret_cast<float *>(ws + plan.off_new);
   a.xch = reinterpret_cast<uint64_t *>(ws + plan.off_xch);
   a.xnew = reinterpret_cast<uint64_t *>(ws + plan.off_xnew);
   a.n_split = plan.n_split;
@@ -323,22 +324,21 @@ nova_kv_status append_step(const nova_kv_params *p, const nova_kv_layout *layout
                                      workspace_bytes, true, a, plan, static_ws, stream);
   if (st != NOVA_KV_OK || batch == 0) return st == NOVA_KV_OK ? ok() : st;
   hipError_t e;
-  // One launch on a table kernel.  With a band whose recent part holds the
-  // new token, in any format and at either head_dim, that token is the band's
-  // last row; otherwise (head_dim 128, plain or fp8 codebooks) it is attended
-  // from its codes, which the splits of a (sequence, KV head) encode between
-  // them: with one split, one workgroup's encoder team would encode all 8
-  // blocks while its token loop runs, and two launches are faster (B = 32,
-  // S = 32K: paged 133 us against 171 us in one launch).  The head_dim-128
-  // band step on a paged cache with one split per unit also runs as encode
-  // then decode (deployed format, B = 32, S = 32K: 166 us against 189 us in
-  // one launch; on a contiguous cache the one launch stays as fast).
-  const bool scaled_format = (p->flags & (NOVA_KV_KEY_SCALE | NOVA_KV_SQ_VALUES)) != 0;
-  const bool fused =
-      plan.use_lut && (band ? band->n_rec >= 1 && (plan.n_split > 1 || !layout->block_table || p->head_dim != 128)
-                            : p->head_dim == 128 && !scaled_format && plan.n_split > 1);
+  // One launch on a table kernel where the plan has the splits' encoder teams
+  // or encoder workgroups append the token (with a band whose recent part holds
+  // it, the token is the band's last row; otherwise it is attended from its
+  // codes); else the one-token encode and the decode.  With one split per unit
+  // a team would encode everything beside its token loop, and two launches are
+  // faster (B = 32, S = 32K: paged 133 us against 171 us in one launch; the
+  // deployed format with a band 166 us against 189 us on a paged cache, the same
+  // on a contiguous one).
+  const bool fused = plan.step != novakv::kStepTwoLaunches;
   if (fused) {
     a.append = 1;
+    if (plan.step == novakv::kStepWorkgroups) {
+      a.enc_per_unit = plan.enc_per_unit;
+      a.n_enc = (batch * p->num_kv_heads * plan.enc_per_unit + 7) & ~7;
+    }
     a.k_new = k_new;
     a.v_new = v_new;
     a.new_bf16 = new_dtype == NOVA_KV_BF16;

@@ -281,10 +281,14 @@ __device__ __forceinline__ void encode_items(const DecodeArgs &a, uint8_t *smem,
 // BSTEP: a fused step with a band (APPEND too): the new token is the band's
 // last row, and the team runs step::encode_token (step_encode.h): task j of
 // the new token's encode goes to split j mod n_eff.
-template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
+// NEW: a step whose token comes from encoder workgroups (step_encode.h): the
+// split that holds its position (has_new) adds it as one more partial of the
+// merge, from its codes, as a decode after the append would.
+template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
 __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, const int b, const int kv,
                                            const int split, const int t0, const int t1, const size_t row0,
-                                           const int rot, const int n_eff, const int S, T4 (&tv)[8]) {
+                                           const int rot, const int n_eff, const int S, T4 (&tv)[8],
+                                           const bool has_new) {
   const uint32_t sbase = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u8_ptr)smem));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -723,18 +727,23 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     }
   };
 
-  auto claim = [&]() -> int {
+  // Up to two rounds per wave the rounds are assigned, so that the result does
+  // not depend on which wave is free first (its reference rounds the fp16
+  // probabilities); a wave saves nothing by claiming there.
+  const bool assigned = nrounds <= 2 * WAVES;
+  auto claim = [&](const int cur) -> int {
+    if (assigned) return cur + WAVES;
     int v = 0;
     if (lane == 0) v = __hip_atomic_fetch_add(rctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     return __builtin_amdgcn_readfirstlane(v);
   };
   int cur = wave;
   while (cur < nrounds) {
-    const int nxt = claim();
+    const int nxt = claim(cur);
     if (nxt < nrounds) load_round(R0 + 64 * nxt, kwb[1], vwb[1], ksb[1], vqb[1]);
     process_round(R0 + 64 * cur, kwb[0], vwb[0], ksb[0], vqb[0]);
     if (nxt >= nrounds) break;
-    const int nxt2 = claim();
+    const int nxt2 = claim(nxt);
     if (nxt2 < nrounds) load_round(R0 + 64 * nxt2, kwb[0], vwb[0], ksb[0], vqb[0]);
     process_round(R0 + 64 * nxt, kwb[1], vwb[1], ksb[1], vqb[1]);
     cur = nxt2;
@@ -774,6 +783,33 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   // still in the loop and the merge, and the last arrival finds them in
   // registers.
   load_tv_rows<TBF>(a, kv, tv);
+  float *newp = reinterpret_cast<float *>(smem + kItemRes);  // the new token: logits [4], value [128]
+  if constexpr (NEW) {
+    // the last wave, which has the fewest rounds of a short split
+    if (has_new && wave == WAVES - 1) {
+      uint32_t code = 0, scale = 0, sq = 0;
+      const bool ok = step::take_new_token<kL, KS, SQ>(a, b * a.num_kv_heads + kv, lane, code, scale, sq);
+      const int g = lane & 31;
+      half4_t e = {0, 0, 0, 0};
+      if (lane < 32) e = *reinterpret_cast<const half4_t *>(smem + code * 256 + g * 8);
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        float z = wave_sum(static_cast<float>(e[h]));
+        if constexpr (KS) z *= __uint_as_float(scale << 16);
+        if (lane == 0) newp[h] = z;
+      }
+      if (lane >= 32) {
+        const half4_t c = *reinterpret_cast<const half4_t *>(smem + kVBase + (g & 7) * 8192 + 32 * code + 8 * (g >> 3));
+        float4 v = make_float4(c[0], c[1], c[2], c[3]);
+        if constexpr (SQ) {
+          const float sc = __uint_as_float(sq << 16), of = __uint_as_float(sq & 0xffff0000u);
+          v = make_float4(fmaf(sc, v.x, of), fmaf(sc, v.y, of), fmaf(sc, v.z, of), fmaf(sc, v.w, of));
+        }
+        if (!ok) v = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""));
+        *reinterpret_cast<float4 *>(newp + 4 + 4 * g) = v;
+      }
+    }
+  }
   if constexpr (APPEND) {
     // the merge region holds the encoder team's scratch until its last item
     if (n_eff > 0 && wave < 8) {
@@ -815,7 +851,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   // LDS and published to the exchange by the threads that form it
   float *own = reinterpret_cast<float *>(smem + kAuxOwn);
   float *ownml = reinterpret_cast<float *>(smem + kAuxCtl) + 8;
-  const bool pub = a.n_split > 1 && act;
+  const bool pub = a.n_split > 1 && (act || (NEW && has_new));
   uint64_t *slot = a.xch + (static_cast<size_t>(bk) * a.n_split + split) * kXchSlotWords;
   for (int i = tid; i < G * kD; i += WAVES * 64) {
     const int h = i / kD, d = i % kD;
@@ -830,6 +866,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     float big = -INFINITY;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) big = fmaxf(big, mv[w]);
+    if (NEW && has_new) big = fmaxf(big, newp[h]);
     float num = 0.f, den = 0.f;
     if (big != -INFINITY) {
 #pragma unroll
@@ -837,6 +874,11 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
         const float wt = (mv[w] == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mv[w] - big);
         num = fmaf(wt, av[w], num);
         den = fmaf(wt, lv[w], den);
+      }
+      if (NEW && has_new) {
+        const float wt = __builtin_amdgcn_exp2f(newp[h] - big);
+        num = fmaf(wt, newp[4 + d], num);
+        den += wt;
       }
     }
     // kept and published as (log-sum-exp, 1, normalised partial), so that the
@@ -876,10 +918,6 @@ __device__ __forceinline__ void band_share(const int nband, const int n_split, c
 // combine runs once per (sequence, KV head) from a cold instruction cache, so
 // its code is kept short: four slots per batch, and many splits are merged in
 // groups (two levels) rather than read in long batches by one workgroup.
-#ifndef NOVA_KV_XCH_BATCH
-#define NOVA_KV_XCH_BATCH 4
-#endif
-constexpr int kXchBatch = NOVA_KV_XCH_BATCH;
 static_assert(kXchBatch <= 48, "a batch's requests stay within the wave's outstanding-load count");
 
 __device__ __forceinline__ uint64_t readlane64(const uint64_t x, const int lane) {
@@ -1276,16 +1314,17 @@ __device__ __forceinline__ void merge_group(const DecodeArgs &a, uint8_t *smem, 
 // The arrival counters live in the workspace and the last split resets its
 // counter to 0, so a decode step is a single launch.
 // TBF: the transforms are stored as bf16 (NOVA_KV_BF16_TRANSFORMS).
-template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
-__global__ void __launch_bounds__(WAVES * 64) decode_lut_d128(DecodeArgs a) {
+// NEW: without a band, the step's token is encoded by other workgroups.
+// Workgroup wg of n_wg.
+template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
+__device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, const int wg, const int n_wg) {
   static_assert(!BSTEP || APPEND, "a band step is a fused step");
   static_assert(!APPEND || BSTEP || !(KS || SQ), "without a band the fused step serves the plain and fp8 formats");
   static_assert(WAVES == 12, "the exchange roles assume 12 waves");
-  __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES, APPEND>()];
   const int tid = threadIdx.x;
   // each XCD takes a contiguous range of the logical workgroup order
   int kv, b, split;
-  unit_of_workgroup(xcd_contiguous(blockIdx.x, gridDim.x), a.n_split, a.b_chunk, a.num_kv_heads, kv, b, split);
+  unit_of_workgroup(xcd_contiguous(wg, n_wg), a.n_split, a.b_chunk, a.num_kv_heads, kv, b, split);
   const int rest = b * a.n_split + split;  // distinct among the workgroups of a KV head
   const int bk = b * a.num_kv_heads + kv;
   const int G = a.gqa;
@@ -1301,7 +1340,10 @@ __global__ void __launch_bounds__(WAVES * 64) decode_lut_d128(DecodeArgs a) {
   const int lo = new_from_codes ? att_lo : spn.code_lo;
   const int tend = new_from_codes ? max(S - 1, att_lo) : spn.code_hi;
   const int t0 = lo + split * a.chunk;  // splits tile the span read from the pools
-  const int t1 = min(tend, lo + (split + 1) * a.chunk);
+  // the split that holds the new token (the last position attended) reads the
+  // pools up to it
+  const bool has_new = NEW && S > 0 && split == (S - 1 - lo) / a.chunk;
+  const int t1 = min(has_new ? S - 1 : tend, lo + (split + 1) * a.chunk);
   const size_t row0 = static_cast<size_t>(b) * a.num_q_heads + kv * G;
   // Fused step: the splits with pool tokens (at least split 0) share the encode
   // of the new token; such a split runs the setup even with no token of its own.
@@ -1314,7 +1356,8 @@ __global__ void __launch_bounds__(WAVES * 64) decode_lut_d128(DecodeArgs a) {
   }
 
   T4 tv[8];
-  split_pass<WAVES, APPEND, KS, FP8, SQ, BSTEP, TBF>(a, smem, b, kv, split, t0, max(t0, t1), row0, rest, items ? n_eff : 0, S, tv);
+  split_pass<WAVES, APPEND, KS, FP8, SQ, BSTEP, TBF, NEW>(a, smem, b, kv, split, t0, max(t0, t1), row0, rest,
+                                                          items ? n_eff : 0, S, tv, has_new);
   // Sink-plus-recent band: this split's share of the band rows, attended in
   // the table's LDS region (free after the split pass) and published beside
   // the split's partial; one CU would read the whole band at a fraction of
@@ -1388,65 +1431,31 @@ __global__ void __launch_bounds__(WAVES * 64) decode_lut_d128(DecodeArgs a) {
   }
 }
 
+template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
+__global__ void __launch_bounds__(WAVES * 64) decode_lut_d128(DecodeArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES, APPEND>()];
+  unit_pass<WAVES, APPEND, KS, FP8, SQ, BSTEP, TBF, false>(a, smem, blockIdx.x, gridDim.x);
+}
+
+// The step without a band, its encoder in workgroups 0 .. n_enc - 1 (a multiple
+// of 8, so the other workgroups keep their XCDs).
+template <int WAVES, bool KS, bool FP8, bool SQ, bool TBF>
+__global__ void __launch_bounds__(WAVES * 64) step_lut_d128(DecodeArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES, false>()];
+  constexpr int TEAMS = WAVES / 4;
+  static_assert(TEAMS * sizeof(step::Scratch<kD>) + 4 * TEAMS <= lds_bytes<WAVES, false>(), "team scratch");
+  if (static_cast<int>(blockIdx.x) < a.n_enc) {
+    const int bsz = a.layout.block_size;
+    const int bs_shift = (bsz & (bsz - 1)) == 0 ? __builtin_ctz(bsz) : -1;
+    step::encode_workgroup<kD, TEAMS, KS, FP8, SQ, TBF>(a, smem, blockIdx.x, [&](const int b, const int kv, const int p) {
+      return subtile_offset(a, b, kv, p & ~15, bs_shift) + static_cast<size_t>(p & 15) * kL;
+    });
+    return;
+  }
+  unit_pass<WAVES, false, KS, FP8, SQ, false, TBF, true>(a, smem, blockIdx.x - a.n_enc, gridDim.x - a.n_enc);
+}
+
 }  // namespace
-
-bool lut_path_eligible(int head_dim, int gqa, int block_size) {
-  return block_size % 16 == 0 && ((head_dim == 128 && gqa <= 4) || (head_dim == 64 && gqa <= 8));
-}
-
-// Splits per (sequence, KV head): enough for about 256 workgroups, one per
-// CU, but never fewer than kMinChunk tokens per split.  Every split pays the
-// whole setup (parameters, query transform, tables) and adds a partial to the
-// combine, so a short span is not worth many CUs: a split of kMinChunk tokens
-// streams its codes in less time than one more partial costs the combine.
-#ifndef NOVA_KV_MIN_CHUNK
-#define NOVA_KV_MIN_CHUNK 512
-#endif
-constexpr int kMinChunk = NOVA_KV_MIN_CHUNK;
-
-void plan_lut(int batch, int num_kv_heads, int max_seq_len, int *n_split, int *chunk) {
-  const long long units = static_cast<long long>(batch) * num_kv_heads;
-  int ns = static_cast<int>((256 + units - 1) / units);
-  if (ns < 1) ns = 1;
-  int ch = (max_seq_len + ns - 1) / ns;
-  ch = (ch + 63) & ~63;
-  if (ch < kMinChunk) ch = kMinChunk;
-  *chunk = ch;
-  *n_split = (max_seq_len + ch - 1) / ch;
-}
-
-// Sequences per block of the table kernels' workgroup order: the largest
-// divisor of batch that leaves about two KV heads (all their splits) in each
-// XCD's eighth of the grid.  Same-box timing at B=8, 8 KV heads, 4 splits:
-// two KV heads per XCD beat both one (32 CUs of one L2 request the same
-// parameter lines at once) and eight (every L2 fetches every KV head's
-// parameters).
-// One combine reads up to kXchBatch other slots in one round trip; above
-// that the splits are merged in groups of about sqrt(n_split) splits (a power
-// of two, at most 32) first.
-#ifndef NOVA_KV_ONE_LEVEL_MAX
-#define NOVA_KV_ONE_LEVEL_MAX (kXchBatch + 1)
-#endif
-#ifndef NOVA_KV_GROUP_MAX
-#define NOVA_KV_GROUP_MAX 32
-#endif
-int plan_group_size(int n_split) {
-  if (n_split <= NOVA_KV_ONE_LEVEL_MAX) return n_split > 0 ? n_split : 1;
-  int gs = 2;
-  while (gs < NOVA_KV_GROUP_MAX && gs * gs < n_split) gs *= 2;
-  return gs;
-}
-
-int plan_b_chunk(int batch, int num_kv_heads, int n_split) {
-  const long long grid = static_cast<long long>(batch) * num_kv_heads * n_split;
-  const long long per_xcd = grid / 8 > 0 ? grid / 8 : 1;
-  long long target = per_xcd / (2LL * n_split);
-  if (target < 1) target = 1;
-  int bc = 1;
-  for (int d = 1; d <= batch && d <= target; ++d)
-    if (batch % d == 0) bc = d;
-  return bc;
-}
 
 template <bool APPEND, bool KS, bool BSTEP, bool TBF>
 void launch_d128(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStream_t stream) {
@@ -1464,9 +1473,22 @@ void launch_d128(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStre
   }
 }
 
+template <bool KS, bool SQ, bool TBF>
+void launch_step_d128(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStream_t stream) {
+  a.cb_fp8 ? step_lut_d128<12, KS, true, SQ, TBF><<<grid, block, 0, stream>>>(a)
+           : step_lut_d128<12, KS, false, SQ, TBF><<<grid, block, 0, stream>>>(a);
+}
+
 template <bool TBF>
 void launch_d128_storage(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStream_t stream) {
-  if (a.append && a.band_k)
+  if (a.append && a.n_enc > 0) {
+    if (a.v_sq)
+      a.k_scales ? launch_step_d128<true, true, TBF>(a, grid, block, stream)
+                 : launch_step_d128<false, true, TBF>(a, grid, block, stream);
+    else
+      a.k_scales ? launch_step_d128<true, false, TBF>(a, grid, block, stream)
+                 : launch_step_d128<false, false, TBF>(a, grid, block, stream);
+  } else if (a.append && a.band_k)
     a.k_scales ? launch_d128<true, true, true, TBF>(a, grid, block, stream)
                : launch_d128<true, false, true, TBF>(a, grid, block, stream);
   else if (a.append)  // plain or fp8 codebooks (checked by the caller)
@@ -1480,8 +1502,11 @@ void launch_d128_storage(const DecodeArgs &a, const dim3 grid, const dim3 block,
 hipError_t launch_decode_lut(const DecodeArgs &a, hipStream_t stream) {
   // A fused step in the key-scale or scalar value format, or with a band,
   // attends its new token as the band's last row: it needs a recent band.
-  if (a.append && (a.k_scales || a.v_sq || a.band_k) && !(a.band_k && a.n_rec >= 1)) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(a.batch * a.num_kv_heads * a.n_split));
+  // Encoder workgroups serve any format without a band.
+  if (a.n_enc > 0 ? (!a.append || a.band_k || a.n_enc % 8 != 0)
+                  : (a.append && (a.k_scales || a.v_sq || a.band_k) && !(a.band_k && a.n_rec >= 1)))
+    return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(a.batch * a.num_kv_heads * a.n_split + a.n_enc));
   const dim3 block(12 * 64);
   a.t_bf16 ? launch_d128_storage<true>(a, grid, block, stream) : launch_d128_storage<false>(a, grid, block, stream);
   return hipGetLastError();

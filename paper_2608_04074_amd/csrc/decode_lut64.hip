@@ -49,6 +49,9 @@ constexpr uint32_t kAuxQ = kVBase + 32768;          // [8][64] f32
 constexpr uint32_t kAuxPart = kAuxQ + kH * kD * 4;  // 10 KB
 constexpr uint32_t kAuxOwn = kAuxPart;
 constexpr uint32_t kAuxOut = kAuxPart + kH * kD * 4;
+// a step's new token: past the split's own partial, in what the combine's
+// outputs take over
+constexpr uint32_t kAuxNew = kAuxPart + 8192;
 constexpr uint32_t kAuxCtl = kAuxPart + 10240;
 // control words (32-bit): [0] arrival state, [1] first arrival, [8..16) shifted
 // sink logits, [16..32) own (m, l)
@@ -91,9 +94,13 @@ __device__ __forceinline__ void load_tv_rows(const DecodeArgs &a, const int kv, 
 
 // (BSTEP: the kernel's own instantiation, so that each kernel inlines a
 // split pass of its own and the plain kernels compile as without the step)
-template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
+// NEW: a step whose token comes from encoder workgroups (step_encode.h): the
+// split that holds its position (has_new) adds it as one more partial of the
+// merge, from its codes.
+template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
 __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, const int b, const int kv,
-                                           const int t0, const int t1, const size_t row0, T4 (&tv)[4]) {
+                                           const int t0, const int t1, const size_t row0, T4 (&tv)[4],
+                                           const bool has_new) {
   const uint32_t sbase = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_u8_ptr)smem));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -122,7 +129,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   for (int X = 0; X < 4; ++X) acc[X] = float4_t{0.f, 0.f, 0.f, 0.f};
 
   const int R0 = t0 & ~(kRound - 1);
-  int nrounds = (t1 - R0 + kRound - 1) / kRound;
+  const int nrounds = NEW && t1 <= t0 ? 0 : (t1 - R0 + kRound - 1) / kRound;  // (a step's split may hold the new token alone)
   const int last16 = (t1 - 1) & ~15;
   const uint8_t *kpool = a.k_codes;
   const uint8_t *vpool = a.v_codes;
@@ -434,6 +441,33 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     }
   }
   load_tv_rows<TBF>(a, kv, tv);
+  float *newp = reinterpret_cast<float *>(smem + kAuxNew);  // the new token: logits [8], value [64]
+  if constexpr (NEW) {
+    // the last wave, which has the fewest rounds of a short split
+    if (has_new && wave == WAVES - 1) {
+      uint32_t code = 0, scale = 0, sq = 0;
+      const bool ok = step::take_new_token<kL, KS, SQ>(a, b * a.num_kv_heads + kv, lane, code, scale, sq);
+      const int g = lane & (kL - 1);
+      half8_t e = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (lane < kL) e = *reinterpret_cast<const half8_t *>(smem + code * 256 + g * 16);
+#pragma unroll
+      for (int h = 0; h < kH; ++h) {
+        float z = wave_sum(static_cast<float>(e[h]));
+        if constexpr (KS) z *= __uint_as_float(scale << 16);
+        if (lane == 0) newp[h] = z;
+      }
+      if (lane >= 32 && lane < 32 + kL) {
+        const half4_t c = *reinterpret_cast<const half4_t *>(smem + kVBase + (g & 3) * 8192 + 32 * code + 8 * (g >> 2));
+        float4 v = make_float4(c[0], c[1], c[2], c[3]);
+        if constexpr (SQ) {
+          const float sc = __uint_as_float(sq << 16), of = __uint_as_float(sq & 0xffff0000u);
+          v = make_float4(fmaf(sc, v.x, of), fmaf(sc, v.y, of), fmaf(sc, v.z, of), fmaf(sc, v.w, of));
+        }
+        if (!ok) v = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""));
+        *reinterpret_cast<float4 *>(newp + kH + 4 * g) = v;
+      }
+    }
+  }
 
   // ---- per-wave reduction: l over the rows of a column; the two set columns
   // of a head (lanes n and n + 8 of a row) are rescaled to a common max and summed
@@ -482,6 +516,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     const int h = i / kD, d = i % kD;
     float big = -INFINITY;
     for (int w = 0; w < WAVES; ++w) big = fmaxf(big, merge[w * kMergeFloats + h]);
+    if (NEW && has_new) big = fmaxf(big, newp[h]);
     float num = 0.f, den = 0.f;
     if (big != -INFINITY) {
       for (int w = 0; w < WAVES; ++w) {
@@ -489,6 +524,11 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
         const float wt = (mwv == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mwv - big);
         num = fmaf(wt, merge[w * kMergeFloats + 2 * kH + h * kD + d], num);
         den = fmaf(wt, merge[w * kMergeFloats + kH + h], den);
+      }
+      if (NEW && has_new) {
+        const float wt = __builtin_amdgcn_exp2f(newp[h] - big);
+        num = fmaf(wt, newp[kH + d], num);
+        den += wt;
       }
     }
     own[i] = num;
@@ -637,13 +677,14 @@ __device__ __forceinline__ void combine_unit(const DecodeArgs &a, uint8_t *smem,
 // token is the band's last row, stored by the combining split; the first
 // split to count in stores its codes (step_encode.h).
 // TBF: the transforms are stored as bf16 (NOVA_KV_BF16_TRANSFORMS).
-template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
-__global__ void __launch_bounds__(WAVES * 64) decode_lut_d64(DecodeArgs a) {
-  __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES>()];
+// NEW: without a band, the step's token is encoded by other workgroups.
+// Workgroup wg of n_wg.
+template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
+__device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, const int wg, const int n_wg) {
   const int tid = threadIdx.x;
   // each XCD takes a contiguous range of the logical workgroup order
   int kv, b, split;
-  unit_of_workgroup(xcd_contiguous(blockIdx.x, gridDim.x), a.n_split, a.b_chunk, a.num_kv_heads, kv, b, split);
+  unit_of_workgroup(xcd_contiguous(wg, n_wg), a.n_split, a.b_chunk, a.num_kv_heads, kv, b, split);
   const int bk = b * a.num_kv_heads + kv;
   const int G = a.gqa;
 
@@ -653,13 +694,16 @@ __global__ void __launch_bounds__(WAVES * 64) decode_lut_d64(DecodeArgs a) {
   const AttendedSpans spn = attended_spans(att_lo, S, a.n_sink, a.n_rec);
   const int lo = spn.code_lo, tend = spn.code_hi;
   const int t0 = lo + split * a.chunk;  // splits tile the span read from the pools
-  const int t1 = min(tend, lo + (split + 1) * a.chunk);
+  // the split that holds the new token (the last position attended) reads the
+  // pools up to it
+  const bool has_new = NEW && S > 0 && split == (S - 1 - lo) / a.chunk;
+  const int t1 = min(has_new ? S - 1 : tend, lo + (split + 1) * a.chunk);
   const size_t row0 = static_cast<size_t>(b) * a.num_q_heads + kv * G;
-  const bool active = t0 < t1;
+  const bool active = t0 < t1 || has_new;
 
   T4 tv[4];
   if (active) {
-    split_pass<WAVES, KS, FP8, SQ, BSTEP, TBF>(a, smem, b, kv, t0, t1, row0, tv);
+    split_pass<WAVES, KS, FP8, SQ, BSTEP, TBF, NEW>(a, smem, b, kv, t0, t1, row0, tv, has_new);
   } else {
     load_tv_rows<TBF>(a, kv, tv);
   }
@@ -730,6 +774,30 @@ __global__ void __launch_bounds__(WAVES * 64) decode_lut_d64(DecodeArgs a) {
   combine_unit<WAVES, BSTEP, TBF>(a, smem, b, kv, row0, split, active, S, lo, tend, att_lo, spn.sink_end, tv);
 }
 
+template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
+__global__ void __launch_bounds__(WAVES * 64) decode_lut_d64(DecodeArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES>()];
+  unit_pass<WAVES, KS, FP8, SQ, BSTEP, TBF, false>(a, smem, blockIdx.x, gridDim.x);
+}
+
+// The step without a band, its encoder in workgroups 0 .. n_enc - 1 (a multiple
+// of 8, so the other workgroups keep their XCDs).
+template <int WAVES, bool KS, bool FP8, bool SQ, bool TBF>
+__global__ void __launch_bounds__(WAVES * 64) step_lut_d64(DecodeArgs a) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES>()];
+  constexpr int TEAMS = WAVES / 4;
+  static_assert(TEAMS * sizeof(step::Scratch<kD>) + 4 * TEAMS <= lds_bytes<WAVES>(), "team scratch");
+  if (static_cast<int>(blockIdx.x) < a.n_enc) {
+    const int bsz = a.layout.block_size;
+    const int bs_shift = (bsz & (bsz - 1)) == 0 ? __builtin_ctz(bsz) : -1;
+    step::encode_workgroup<kD, TEAMS, KS, FP8, SQ, TBF>(a, smem, blockIdx.x, [&](const int b, const int kv, const int p) {
+      return subtile_offset(a, b, kv, p & ~15, bs_shift) + static_cast<size_t>(p & 15) * kL;
+    });
+    return;
+  }
+  unit_pass<WAVES, KS, FP8, SQ, false, TBF, true>(a, smem, blockIdx.x - a.n_enc, gridDim.x - a.n_enc);
+}
+
 }  // namespace
 
 template <bool BSTEP, bool TBF>
@@ -751,13 +819,37 @@ void launch_d64(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStrea
   }
 }
 
+template <bool TBF>
+void launch_step_d64(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStream_t stream) {
+  constexpr int W = 16;
+  if (a.v_sq) {
+    if (a.k_scales)
+      a.cb_fp8 ? step_lut_d64<W, true, true, true, TBF><<<grid, block, 0, stream>>>(a)
+               : step_lut_d64<W, true, false, true, TBF><<<grid, block, 0, stream>>>(a);
+    else
+      a.cb_fp8 ? step_lut_d64<W, false, true, true, TBF><<<grid, block, 0, stream>>>(a)
+               : step_lut_d64<W, false, false, true, TBF><<<grid, block, 0, stream>>>(a);
+  } else if (a.k_scales) {
+    a.cb_fp8 ? step_lut_d64<W, true, true, false, TBF><<<grid, block, 0, stream>>>(a)
+             : step_lut_d64<W, true, false, false, TBF><<<grid, block, 0, stream>>>(a);
+  } else {
+    a.cb_fp8 ? step_lut_d64<W, false, true, false, TBF><<<grid, block, 0, stream>>>(a)
+             : step_lut_d64<W, false, false, false, TBF><<<grid, block, 0, stream>>>(a);
+  }
+}
+
 hipError_t launch_decode_lut64(const DecodeArgs &a, hipStream_t stream) {
   // 16 waves, 4 per SIMD: the kernel fits in 128 VGPRs.  A step (append) runs
   // here only with a band whose recent part holds the new token.
-  if (a.append && !(a.band_k && a.n_rec >= 1)) return hipErrorInvalidValue;
-  const dim3 grid(static_cast<unsigned>(a.batch * a.num_kv_heads * a.n_split));
+  // (its encoder then in the first split to arrive), or without one with
+  // encoder workgroups.
+  if (a.n_enc > 0 ? (!a.append || a.band_k || a.n_enc % 8 != 0) : (a.append && !(a.band_k && a.n_rec >= 1)))
+    return hipErrorInvalidValue;
+  const dim3 grid(static_cast<unsigned>(a.batch * a.num_kv_heads * a.n_split + a.n_enc));
   const dim3 block(16 * 64);
-  if (a.t_bf16)
+  if (a.n_enc > 0)
+    a.t_bf16 ? launch_step_d64<true>(a, grid, block, stream) : launch_step_d64<false>(a, grid, block, stream);
+  else if (a.t_bf16)
     a.append ? launch_d64<true, true>(a, grid, block, stream) : launch_d64<false, true>(a, grid, block, stream);
   else
     a.append ? launch_d64<true, false>(a, grid, block, stream) : launch_d64<false, false>(a, grid, block, stream);

@@ -102,6 +102,14 @@ __device__ __forceinline__ void split_f16(float x, _Float16 &hi, _Float16 &lo) {
   lo = static_cast<_Float16>((x - static_cast<float>(hi)) * kLoUp);
 }
 
+// Scalar value arm: a code byte's four levels minus 1.5 (exact in fp16).
+__device__ __forceinline__ uint2 centred_levels(const uint32_t c) {
+  const uint2 q = sq_unpack_f16(c);
+  const half2_t half3 = {static_cast<_Float16>(1.5f), static_cast<_Float16>(1.5f)};
+  return make_uint2(__builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, q.x) - half3),
+                    __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2_t, q.y) - half3));
+}
+
 // Running reference of a softmax column.
 struct Lag {
   float m;
@@ -236,7 +244,7 @@ __global__ void __launch_bounds__(kNT) decode_vq(DecodeArgs a) {
       for (int k = 0; k < CPER; ++k) {
         const int e = min(tid + k * kNT, L * 256 - 1), g = e >> 8, c = e & 255;
         *reinterpret_cast<uint2 *>(smem + S_::kV + (g % GP) * 8192 + 32 * c + 8 * (g / GP)) =
-            SQ ? sq_unpack_f16(c) : codeword_f16(vst[k], FP8);
+            SQ ? centred_levels(c) : codeword_f16(vst[k], FP8);
       }
     }
     __syncthreads();
@@ -312,7 +320,7 @@ __global__ void __launch_bounds__(kNT) decode_vq(DecodeArgs a) {
 
   // ---- token loop
   Lag ref{-INFINITY}, ref2{-INFINITY};  // ref2 (scalar value arm): of the probabilities times the token's scale
-  float l_run = 0.f, z_run = 0.f;       // z_run: sum of p * offset
+  float l_run = 0.f, z_run = 0.f;       // z_run: sum of p * (offset + 1.5 scale)
   float4_t acc[NX];
 #pragma unroll
   for (int X = 0; X < NX; ++X) acc[X] = float4_t{0.f, 0.f, 0.f, 0.f};
@@ -371,15 +379,17 @@ __global__ void __launch_bounds__(kNT) decode_vq(DecodeArgs a) {
       }
       l_run = fmaf(l_run, alpha, lsum);
       if constexpr (SQ) {
-        // offsets are summed in fp32; the levels' weights p * scale have a
-        // reference of their own, so that any scale stays in fp16 range
+        // value = (offset + 1.5 scale) + scale (level - 1.5): the two sums are
+        // small, where offset and scale * level would cancel.  The first is
+        // formed in fp32; the levels' weights p * scale have a reference of
+        // their own, so that any scale stays in fp16 range
         float zs = 0.f, ymax = -INFINITY, mant[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) {
           uint32_t g = static_cast<uint32_t>(__shfl(static_cast<int>(r.vq), 16 * (j >> 2) + 4 * tau + (j & 3)));
           if (ragged && z[j] == -INFINITY) g = 0u;  // rows past the tokens may hold anything
-          zs = fmaf(w[j], __uint_as_float(g & 0xffff0000u), zs);
           const float scale = __uint_as_float(g << 16);
+          zs = fmaf(w[j], fmaf(1.5f, scale, __uint_as_float(g & 0xffff0000u)), zs);
           mant[j] = __builtin_amdgcn_frexp_mantf(scale);
           z[j] += static_cast<float>(__builtin_amdgcn_frexp_expf(scale));
           ymax = fmaxf(ymax, z[j]);

@@ -782,15 +782,15 @@ void launch_tiles(const EncodeArgs &a, hipStream_t stream) {
 }
 
 // Few tokens in the plain formats: encode_small, a workgroup per token, side and
-// eight groups, as long as its workgroups stay below about six per CU (8 KV
-// heads of 128, one token per sequence: 7.8 us against 10.1 us in tiles for 16
-// sequences, 12.6 against 10.6 for 32).  The key scale and the scalar arm need
+// eight groups, as long as its workgroups stay below four per CU (8 KV
+// heads of 128, one token per sequence: 5.6 us against 7.5 us in tiles for 8
+// sequences, 7.5 both for 16, 12.6 against 8.1 for 32).  The key scale and the scalar arm need
 // a token's whole transform, which the tiles form once (one sequence, both
 // formats: 10.8 us against 13.8 with a workgroup per token and block).
 template <int D, bool TBF>
 hipError_t launch_encode_t(const EncodeArgs &a, hipStream_t stream) {
   const long long blocks = 2ll * (D / kGroupDim / encblk::kGroups) * a.n_new;
-  if (!a.k_scales && !a.v_sq && blocks * a.batch * a.num_kv_heads <= 1536) {
+  if (!a.k_scales && !a.v_sq && blocks * a.batch * a.num_kv_heads < 1024) {
     const dim3 grid(static_cast<unsigned>(blocks), a.num_kv_heads, a.batch);
     if (a.cb_fp8)
       encode_small<D, true, TBF><<<grid, dim3(256), 0, stream>>>(a);

@@ -77,7 +77,11 @@ struct DecodeArgs {
   uint8_t *k_codes_w, *v_codes_w;  // the pools k_codes / v_codes, written at the new position
   uint16_t *k_scales_w, *v_sq_w;   // the key-scale and scalar-arm pools, written there (else nullptr)
   uint16_t *band_k_w, *band_v_w;   // the band buffers, written at the new token's slot (else nullptr)
-  float *newp;      // [B][Hkv][8 items][32] per-block results for the new token
+  // Fused step without a band, on a launch that leaves CUs idle: workgroups
+  // 0 .. n_enc - 1 encode (enc_per_unit per unit; step_encode.h), the others
+  // decode, and the split that holds position seq_lens[b] - 1 takes that
+  // token from xnew.  n_enc = 0: the splits' encoder teams do it.
+  int n_enc, enc_per_unit;
   // Tagged exchange of the head_dim-128 table kernel (64-bit words, the tag
   // in the high half): split partials [B*Hkv][n_split][kXchSlotWords] and
   // the new token's per-block results [B*Hkv][8 items][32].
@@ -100,6 +104,8 @@ struct DecodeArgs {
 // accumulators).
 constexpr int kXchBandWords = 16 + 512;
 constexpr int kXchSlotWords = 2 * kXchBandWords;
+// Slots that a combine of the head_dim-128 table kernel requests before it waits.
+constexpr int kXchBatch = 4;
 
 struct EncodeArgs {
   int batch, n_new, num_kv_heads, head_dim;
@@ -144,19 +150,35 @@ __host__ __device__ __forceinline__ AttendedSpans attended_spans(int lo, int S, 
   return sp;
 }
 
+// What a step call (append, then decode) adds to its plan.
+struct StepFormat {
+  bool scaled;   // key scale or scalar value arm
+  bool no_band;
+  bool in_band;  // a band whose recent part holds the new token
+  bool paged;
+  int tasks;     // encoder tasks of one token (step_encode.h): blocks of 8 groups, or whole tokens
+};
+// How the step's token is encoded: by a launch of its own, by the splits'
+// encoder teams, or by workgroups of the decode launch.
+enum StepMode { kStepTwoLaunches, kStepTeams, kStepWorkgroups };
+
 // Split plan and workspace carve-out of the decode path.
 struct DecodePlan {
+  StepMode step;
+  int enc_per_unit;
   int use_lut;      // 1: table kernels (decode_lut.hip, decode_lut64.hip), 0: decode_vq.hip
   int n_split;
   int chunk;
-  size_t off_cnt, off_ml, off_acc, off_new, off_xch, off_xnew, off_xgrp, total;
+  size_t off_cnt, off_ml, off_acc, off_xch, off_xnew, off_xgrp, total;
 };
 // Splits tile each sequence's attended span (the last `window` tokens, or all).
 // The workspace (off_*, total) is sized for every window and both decode
 // paths, so it depends only on (batch, heads, head_dim, max_seq_len);
 // block_size <= 0 asks for that size alone.
-DecodePlan plan_decode(int batch, int num_q_heads, int num_kv_heads, int head_dim,
-                       int max_seq_len, int block_size, int window);
+// `band_rows`: rows of the call's band; `step`: the plan of a step call in that
+// format (nullptr: a decode).
+DecodePlan plan_decode(int batch, int num_q_heads, int num_kv_heads, int head_dim, int max_seq_len, int block_size,
+                       int window, int band_rows = 0, const StepFormat *step = nullptr);
 
 hipError_t launch_decode(const DecodeArgs &a, int use_lut, hipStream_t stream);
 int plan_b_chunk(int batch, int num_kv_heads, int n_split);
@@ -167,7 +189,6 @@ int plan_group_size(int n_split);
 // heads per KV head; 16-token-aligned blocks): query transform, split pass and
 // combine in one launch.
 bool lut_path_eligible(int head_dim, int gqa, int block_size);
-void plan_lut(int batch, int num_kv_heads, int max_seq_len, int *n_split, int *chunk);
 hipError_t launch_decode_lut(const DecodeArgs &a, hipStream_t stream);    // head_dim 128
 hipError_t launch_decode_lut64(const DecodeArgs &a, hipStream_t stream);  // head_dim 64
 // Everything else: up to kMaxGqa query heads per KV head, any block size.

@@ -20,6 +20,7 @@
 #pragma once
 
 #include "encode_block.h"
+#include "lut_common.h"
 #include "nova_kv_internal.h"
 
 namespace novakv {
@@ -63,13 +64,21 @@ struct Scratch {
   uint8_t q[2][D];             // its scalar-arm levels
 };
 
+// Words of a new token handed to the split that attends it (DecodeArgs::xnew):
+// key code of group g, value code of group g, key scale, scalar-arm word.
+constexpr int kWordK = 0, kWordV = 32, kWordScale = 64, kWordSq = 65;
+struct NoPublish {
+  __device__ __forceinline__ void operator()(int, uint32_t) const {}
+};
+
 // Tasks first, first + stride, ... of the new token at code row offset tokoff
-// of the pools, by team thread t (0..255); meet() is the team's meeting.
+// of the pools, by team thread t (0..255); meet() is the team's meeting, and
+// publish(word, value) gets every stored value.
 // TBF: the transforms are stored as bf16.
-template <int D, bool KS, bool SQ, bool TBF, class Meet>
+template <int D, bool KS, bool SQ, bool TBF, class Meet, class Publish = NoPublish>
 __device__ __forceinline__ void encode_token(const DecodeArgs &a, Scratch<D> &ls, const int b, const int kv,
                                              const int first, const int stride, const size_t tokoff, const int t,
-                                             const bool fp8, Meet meet) {
+                                             const bool fp8, Meet meet, Publish publish = NoPublish()) {
   using T = Tasks<D, KS, SQ>;
   constexpr int L = D / kGroupDim;
   const size_t elem = (static_cast<size_t>(b) * a.num_kv_heads + kv) * D + (t & (D - 1));
@@ -113,20 +122,32 @@ __device__ __forceinline__ void encode_token(const DecodeArgs &a, Scratch<D> &ls
             uu[i] = rho > 0.0 ? v / rho : 0.0;
           }
           const int code = encblk::search_codes(t, uu, cw, fp8);
-          if ((t & 31) == 0) a.k_codes_w[tokoff + encblk::kGroups * bb + (t >> 5)] = static_cast<uint8_t>(code);
+          if ((t & 31) == 0) {
+            const int g = encblk::kGroups * bb + (t >> 5);
+            a.k_codes_w[tokoff + g] = static_cast<uint8_t>(code);
+            publish(kWordK + g, static_cast<uint32_t>(code));
+          }
           if (bb + 1 < T::kBlocks) {
 #pragma unroll
             for (int i = 0; i < encblk::kPer; ++i) cw[i] = nx[i];
           }
         }
-        if (t == 0) a.k_scales_w[tokoff / L] = encblk::bf16_of(rho);
+        if (t == 0) {
+          a.k_scales_w[tokoff / L] = encblk::bf16_of(rho);
+          publish(kWordScale, encblk::bf16_of(rho));
+        }
       } else {
         uint16_t sbits, zbits;
         encblk::sq_levels<D>(t, u, ls.red[k & 1], ls.q[k & 1], meet, sbits, zbits);
-        if (t < L) a.v_codes_w[tokoff + t] = encblk::sq_byte(ls.q[k & 1], t);
+        if (t < L) {
+          const uint8_t levels = encblk::sq_byte(ls.q[k & 1], t);
+          a.v_codes_w[tokoff + t] = levels;
+          publish(kWordV + t, levels);
+        }
         if (t == 0) {
           a.v_sq_w[(tokoff / L) * 2] = sbits;
           a.v_sq_w[(tokoff / L) * 2 + 1] = zbits;
+          publish(kWordSq, sbits | (static_cast<uint32_t>(zbits) << 16));
         }
       }
     } else {
@@ -137,8 +158,11 @@ __device__ __forceinline__ void encode_token(const DecodeArgs &a, Scratch<D> &ls
       encblk::partial_block<D>(t, s, rows, TBF);
       meet();
       const int code = encblk::search_block<D>(t, s, cw, fp8);
-      if ((t & 31) == 0)
-        (key ? a.k_codes_w : a.v_codes_w)[tokoff + encblk::kGroups * blk + (t >> 5)] = static_cast<uint8_t>(code);
+      if ((t & 31) == 0) {
+        const int g = encblk::kGroups * blk + (t >> 5);
+        (key ? a.k_codes_w : a.v_codes_w)[tokoff + g] = static_cast<uint8_t>(code);
+        publish((key ? kWordK : kWordV) + g, static_cast<uint32_t>(code));
+      }
     }
   }
   meet();  // every read of the scratch is done
@@ -163,6 +187,74 @@ __device__ __forceinline__ void store_band_rows(const DecodeArgs &a, const int b
   const int nb = a.n_sink + a.n_rec;
   (side ? a.band_v_w : a.band_k_w)[((static_cast<size_t>(b) * a.num_kv_heads + kv) * nb +
                                     band_slot(pos, a.n_sink, a.n_rec)) * D + d] = bits;
+}
+
+// ---- the step's encode in workgroups of its own
+//
+// Without a band, where a launch leaves CUs idle, the step's token is encoded
+// by workgroups of the same launch that do nothing else: workgroups 0 ..
+// n_enc - 1, enc_per_unit for each (sequence, KV head), each with TEAMS teams.
+// They hand the token's values to the split that holds its position as tagged
+// words, while that split is still in its setup or token loop.  They come
+// first in the dispatch order, so they run whatever waits for them.
+
+// An encoder workgroup's work (workgroup wg < n_enc).
+template <int D, int TEAMS, bool KS, bool FP8, bool SQ, bool TBF, class RowOf>
+__device__ __forceinline__ void encode_workgroup(const DecodeArgs &a, uint8_t *smem, const int wg, RowOf row_of) {
+  const int unit = wg / a.enc_per_unit, e = wg - unit * a.enc_per_unit;
+  if (unit >= a.batch * a.num_kv_heads) return;  // n_enc is rounded up
+  const int b = unit / a.num_kv_heads, kv = unit - b * a.num_kv_heads;
+  const int S = a.seq_lens[b];
+  if (S <= 0) return;
+  const int tid = threadIdx.x, team = tid >> 8;
+  Scratch<D> *ls = reinterpret_cast<Scratch<D> *>(smem);
+  int *ctr = reinterpret_cast<int *>(smem + TEAMS * sizeof(Scratch<D>));
+  if (tid < TEAMS) ctr[tid] = 0;
+  __syncthreads();
+  uint64_t *xn = a.xnew + static_cast<size_t>(unit) * 8 * 32;
+  int phase = 0;  // shared by every copy of the meeting
+  auto meet = [&] { team_meet(ctr + team, ++phase); };
+  auto publish = [&](const int w, const uint32_t v) { lut::put_word(a.epoch, xn + w, __uint_as_float(v)); };
+  encode_token<D, KS, SQ, TBF>(a, ls[team], b, kv, e * TEAMS + team, TEAMS * a.enc_per_unit, row_of(b, kv, S - 1),
+                               tid & 255, FP8, meet, publish);
+}
+
+// The handed-over words of a unit's new token, read by one whole wave: lane l
+// gets words l (key codes in lanes 0 .., value codes in lanes 32 ..), and
+// every lane the scale and the scalar-arm word in their formats.  A captured
+// call empties them, as replays repeat its tag.  False if a word never came
+// (not expected).
+constexpr int kNewSpin = 1 << 20;
+template <int L, bool KS, bool SQ>
+__device__ __forceinline__ bool take_new_token(const DecodeArgs &a, const int unit, const int lane, uint32_t &code,
+                                               uint32_t &scale, uint32_t &sq) {
+  uint64_t *xn = a.xnew + static_cast<size_t>(unit) * 8 * 32;
+  const int w = (lane & 32) + (lane & (L - 1));
+  uint64_t c, ks = 0, vq = 0;
+  for (int n = 0;; ++n) {
+    c = lut::get_word(xn + w);
+    bool ready = lut::word_ready(a.epoch, c);
+    if constexpr (KS) {
+      ks = lut::get_word(xn + kWordScale);
+      ready = ready && lut::word_ready(a.epoch, ks);
+    }
+    if constexpr (SQ) {
+      vq = lut::get_word(xn + kWordSq);
+      ready = ready && lut::word_ready(a.epoch, vq);
+    }
+    if (__all(ready)) break;
+    if (n == kNewSpin) return false;
+    __builtin_amdgcn_s_sleep(2);
+  }
+  code = static_cast<uint32_t>(c) & 0xffu;
+  scale = static_cast<uint32_t>(ks);
+  sq = static_cast<uint32_t>(vq);
+  if (a.clear_xch) {
+    lut::clear_word(xn + w);
+    if (KS && lane == 0) lut::clear_word(xn + kWordScale);
+    if (SQ && lane == 0) lut::clear_word(xn + kWordSq);
+  }
+  return true;
 }
 
 }  // namespace step
