@@ -30,9 +30,9 @@ int workspace_splits(int batch, int num_kv_heads, int max_seq_len) {
 //
 // A step adds its token's encode, the cheapest of:
 //   workgroups  where units * (splits + 1..) fit the CUs (step_encode.h): next to
-//               nothing, the split with the newest position meets the words
-//               on its way (a step of 2000 tokens, 8 KV heads: 19.7 us by
-//               teams, 18.4 us in two launches);
+//               nothing (a step of 2000 tokens, 8 KV heads: 14.9 us, against 19.6
+//               by teams and 18.4 in two launches; in the deployed format
+//               with a band 22.9 against 31.0);
 //   teams       the splits encode between them, beside their token loops: about
 //               2.5 us and 3 us per item that the loop does not hide (head_dim
 //               128 without a scaled format, or any format with a band);
@@ -78,11 +78,12 @@ Splits plan_splits(const SplitCost &c, const int units, const int span, const in
           s.step = kStepTeams;
         }
       }
-      const int free = kCUs / units - n;  // workgroups a unit may add
-      if (workgroups_ok && free >= 1) {
+      const int free = kCUs / units - n;  // workgroups a unit may add within the round
+      const int want = workgroups_ok ? (step->tasks + c.teams - 1) / c.teams : 0;
+      if (want > 0 && free >= 1) {
         extra = 0;
         s.step = kStepWorkgroups;
-        s.enc_per_unit = std::min(free, (step->tasks + c.teams - 1) / c.teams);
+        s.enc_per_unit = std::min(free, want);
       }
       cost += extra;
     }
@@ -159,7 +160,7 @@ DecodePlan plan_decode(int batch, int num_q_heads, int num_kv_heads, int head_di
     // an only split.
     const bool teams_ok = p.use_lut && step && (step->in_band || (step->no_band && head_dim == 128 && !step->scaled));
     const bool one_split_ok = step && step->in_band && (head_dim == 64 || !step->paged);
-    const bool workgroups_ok = p.use_lut && step && step->no_band;
+    const bool workgroups_ok = p.use_lut && step && (step->no_band || step->in_band);
     const Splits s =
         plan_splits(cost, static_cast<int>(units), span, limit, band_rows, step, teams_ok, one_split_ok, workgroups_ok);
     p.n_split = s.n_split;

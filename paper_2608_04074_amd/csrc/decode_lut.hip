@@ -281,10 +281,10 @@ __device__ __forceinline__ void encode_items(const DecodeArgs &a, uint8_t *smem,
 // BSTEP: a fused step with a band (APPEND too): the new token is the band's
 // last row, and the team runs step::encode_token (step_encode.h): task j of
 // the new token's encode goes to split j mod n_eff.
-// NEW: a step whose token comes from encoder workgroups (step_encode.h): the
-// split that holds its position (has_new) adds it as one more partial of the
-// merge, from its codes, as a decode after the append would.
-template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
+// NEW == kNewCodes: a step whose token comes from encoder workgroups
+// (step_encode.h): the split that holds its position (has_new) adds it as one
+// more partial of the merge, from its codes, as a decode after the append would.
+template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, int NEW>
 __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, const int b, const int kv,
                                            const int split, const int t0, const int t1, const size_t row0,
                                            const int rot, const int n_eff, const int S, T4 (&tv)[8],
@@ -784,7 +784,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   // registers.
   load_tv_rows<TBF>(a, kv, tv);
   float *newp = reinterpret_cast<float *>(smem + kItemRes);  // the new token: logits [4], value [128]
-  if constexpr (NEW) {
+  if constexpr (NEW == step::kNewCodes) {
     // the last wave, which has the fewest rounds of a short split
     if (has_new && wave == WAVES - 1) {
       uint32_t code = 0, scale = 0, sq = 0;
@@ -851,7 +851,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   // LDS and published to the exchange by the threads that form it
   float *own = reinterpret_cast<float *>(smem + kAuxOwn);
   float *ownml = reinterpret_cast<float *>(smem + kAuxCtl) + 8;
-  const bool pub = a.n_split > 1 && (act || (NEW && has_new));
+  const bool pub = a.n_split > 1 && (act || has_new);
   uint64_t *slot = a.xch + (static_cast<size_t>(bk) * a.n_split + split) * kXchSlotWords;
   for (int i = tid; i < G * kD; i += WAVES * 64) {
     const int h = i / kD, d = i % kD;
@@ -866,7 +866,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     float big = -INFINITY;
 #pragma unroll
     for (int w = 0; w < WAVES; ++w) big = fmaxf(big, mv[w]);
-    if (NEW && has_new) big = fmaxf(big, newp[h]);
+    if (has_new) big = fmaxf(big, newp[h]);
     float num = 0.f, den = 0.f;
     if (big != -INFINITY) {
 #pragma unroll
@@ -875,7 +875,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
         num = fmaf(wt, av[w], num);
         den = fmaf(wt, lv[w], den);
       }
-      if (NEW && has_new) {
+      if (has_new) {
         const float wt = __builtin_amdgcn_exp2f(newp[h] - big);
         num = fmaf(wt, newp[4 + d], num);
         den += wt;
@@ -1314,9 +1314,9 @@ __device__ __forceinline__ void merge_group(const DecodeArgs &a, uint8_t *smem, 
 // The arrival counters live in the workspace and the last split resets its
 // counter to 0, so a decode step is a single launch.
 // TBF: the transforms are stored as bf16 (NOVA_KV_BF16_TRANSFORMS).
-// NEW: without a band, the step's token is encoded by other workgroups.
+// NEW: a step whose token other workgroups encode (step_encode.h).
 // Workgroup wg of n_wg.
-template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
+template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, int NEW>
 __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, const int wg, const int n_wg) {
   static_assert(!BSTEP || APPEND, "a band step is a fused step");
   static_assert(!APPEND || BSTEP || !(KS || SQ), "without a band the fused step serves the plain and fp8 formats");
@@ -1342,7 +1342,7 @@ __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, co
   const int t0 = lo + split * a.chunk;  // splits tile the span read from the pools
   // the split that holds the new token (the last position attended) reads the
   // pools up to it
-  const bool has_new = NEW && S > 0 && split == (S - 1 - lo) / a.chunk;
+  const bool has_new = NEW == step::kNewCodes && S > 0 && split == (S - 1 - lo) / a.chunk;
   const int t1 = min(has_new ? S - 1 : tend, lo + (split + 1) * a.chunk);
   const size_t row0 = static_cast<size_t>(b) * a.num_q_heads + kv * G;
   // Fused step: the splits with pool tokens (at least split 0) share the encode
@@ -1368,7 +1368,7 @@ __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, co
     band_share(nband, a.n_split, split, bfirst, bcount);
     if (bcount > 0) {
       using BL = BandLds<kD, 4, WAVES>;
-      if constexpr (BSTEP) {
+      if constexpr (BSTEP || NEW == step::kNewBand) {
         // a fused step's new token is the band's last row: the split that
         // attends it stores it, and reads it back after the barrier
         if (bfirst + bcount == nband) {
@@ -1434,25 +1434,30 @@ __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, co
 template <int WAVES, bool APPEND, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
 __global__ void __launch_bounds__(WAVES * 64) decode_lut_d128(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES, APPEND>()];
-  unit_pass<WAVES, APPEND, KS, FP8, SQ, BSTEP, TBF, false>(a, smem, blockIdx.x, gridDim.x);
+  unit_pass<WAVES, APPEND, KS, FP8, SQ, BSTEP, TBF, step::kNewNone>(a, smem, blockIdx.x, gridDim.x);
 }
 
-// The step without a band, its encoder in workgroups 0 .. n_enc - 1 (a multiple
-// of 8, so the other workgroups keep their XCDs).
-template <int WAVES, bool KS, bool FP8, bool SQ, bool TBF>
+// The step with its encoder in n_enc workgroups of the launch: without a band
+// the first ones (a multiple of 8, so the others keep their XCDs), which a
+// decoding workgroup may wait for; with one the last ones.
+template <int WAVES, bool KS, bool FP8, bool SQ, bool TBF, bool BAND>
 __global__ void __launch_bounds__(WAVES * 64) step_lut_d128(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES, false>()];
   constexpr int TEAMS = WAVES / 4;
-  static_assert(TEAMS * sizeof(step::Scratch<kD>) + 4 * TEAMS <= lds_bytes<WAVES, false>(), "team scratch");
-  if (static_cast<int>(blockIdx.x) < a.n_enc) {
+  static_assert(TEAMS * (sizeof(step::Scratch<kD>) + step::kWide + 4) <= lds_bytes<WAVES, false>(), "team scratch");
+  const int n_main = static_cast<int>(gridDim.x) - a.n_enc;
+  const int wg = static_cast<int>(blockIdx.x);
+  if (BAND ? wg >= n_main : wg < a.n_enc) {
     const int bsz = a.layout.block_size;
     const int bs_shift = (bsz & (bsz - 1)) == 0 ? __builtin_ctz(bsz) : -1;
-    step::encode_workgroup<kD, TEAMS, KS, FP8, SQ, TBF>(a, smem, blockIdx.x, [&](const int b, const int kv, const int p) {
-      return subtile_offset(a, b, kv, p & ~15, bs_shift) + static_cast<size_t>(p & 15) * kL;
-    });
+    step::encode_workgroup<kD, TEAMS, KS, FP8, SQ, TBF, !BAND>(
+        a, smem, BAND ? wg - n_main : wg, [&](const int b, const int kv, const int p) {
+          return subtile_offset(a, b, kv, p & ~15, bs_shift) + static_cast<size_t>(p & 15) * kL;
+        });
     return;
   }
-  unit_pass<WAVES, false, KS, FP8, SQ, false, TBF, true>(a, smem, blockIdx.x - a.n_enc, gridDim.x - a.n_enc);
+  unit_pass<WAVES, false, KS, FP8, SQ, false, TBF, BAND ? step::kNewBand : step::kNewCodes>(
+      a, smem, BAND ? wg : wg - a.n_enc, n_main);
 }
 
 }  // namespace
@@ -1475,8 +1480,12 @@ void launch_d128(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStre
 
 template <bool KS, bool SQ, bool TBF>
 void launch_step_d128(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStream_t stream) {
-  a.cb_fp8 ? step_lut_d128<12, KS, true, SQ, TBF><<<grid, block, 0, stream>>>(a)
-           : step_lut_d128<12, KS, false, SQ, TBF><<<grid, block, 0, stream>>>(a);
+  if (a.band_k)
+    a.cb_fp8 ? step_lut_d128<12, KS, true, SQ, TBF, true><<<grid, block, 0, stream>>>(a)
+             : step_lut_d128<12, KS, false, SQ, TBF, true><<<grid, block, 0, stream>>>(a);
+  else
+    a.cb_fp8 ? step_lut_d128<12, KS, true, SQ, TBF, false><<<grid, block, 0, stream>>>(a)
+             : step_lut_d128<12, KS, false, SQ, TBF, false><<<grid, block, 0, stream>>>(a);
 }
 
 template <bool TBF>
@@ -1502,8 +1511,8 @@ void launch_d128_storage(const DecodeArgs &a, const dim3 grid, const dim3 block,
 hipError_t launch_decode_lut(const DecodeArgs &a, hipStream_t stream) {
   // A fused step in the key-scale or scalar value format, or with a band,
   // attends its new token as the band's last row: it needs a recent band.
-  // Encoder workgroups serve any format without a band.
-  if (a.n_enc > 0 ? (!a.append || a.band_k || a.n_enc % 8 != 0)
+  // Encoder workgroups serve any format, without a band or with such a one.
+  if (a.n_enc > 0 ? (!a.append || a.n_enc % 8 != 0 || (a.band_k && a.n_rec < 1))
                   : (a.append && (a.k_scales || a.v_sq || a.band_k) && !(a.band_k && a.n_rec >= 1)))
     return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(a.batch * a.num_kv_heads * a.n_split + a.n_enc));

@@ -94,10 +94,10 @@ __device__ __forceinline__ void load_tv_rows(const DecodeArgs &a, const int kv, 
 
 // (BSTEP: the kernel's own instantiation, so that each kernel inlines a
 // split pass of its own and the plain kernels compile as without the step)
-// NEW: a step whose token comes from encoder workgroups (step_encode.h): the
-// split that holds its position (has_new) adds it as one more partial of the
-// merge, from its codes.
-template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
+// NEW == kNewCodes: a step whose token comes from encoder workgroups
+// (step_encode.h): the split that holds its position (has_new) adds it as one
+// more partial of the merge, from its codes.
+template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, int NEW>
 __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, const int b, const int kv,
                                            const int t0, const int t1, const size_t row0, T4 (&tv)[4],
                                            const bool has_new) {
@@ -129,7 +129,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   for (int X = 0; X < 4; ++X) acc[X] = float4_t{0.f, 0.f, 0.f, 0.f};
 
   const int R0 = t0 & ~(kRound - 1);
-  const int nrounds = NEW && t1 <= t0 ? 0 : (t1 - R0 + kRound - 1) / kRound;  // (a step's split may hold the new token alone)
+  const int nrounds = NEW == step::kNewCodes && t1 <= t0 ? 0 : (t1 - R0 + kRound - 1) / kRound;  // (a step's split may hold the new token alone)
   const int last16 = (t1 - 1) & ~15;
   const uint8_t *kpool = a.k_codes;
   const uint8_t *vpool = a.v_codes;
@@ -442,7 +442,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   }
   load_tv_rows<TBF>(a, kv, tv);
   float *newp = reinterpret_cast<float *>(smem + kAuxNew);  // the new token: logits [8], value [64]
-  if constexpr (NEW) {
+  if constexpr (NEW == step::kNewCodes) {
     // the last wave, which has the fewest rounds of a short split
     if (has_new && wave == WAVES - 1) {
       uint32_t code = 0, scale = 0, sq = 0;
@@ -516,7 +516,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     const int h = i / kD, d = i % kD;
     float big = -INFINITY;
     for (int w = 0; w < WAVES; ++w) big = fmaxf(big, merge[w * kMergeFloats + h]);
-    if (NEW && has_new) big = fmaxf(big, newp[h]);
+    if (has_new) big = fmaxf(big, newp[h]);
     float num = 0.f, den = 0.f;
     if (big != -INFINITY) {
       for (int w = 0; w < WAVES; ++w) {
@@ -525,7 +525,7 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
         num = fmaf(wt, merge[w * kMergeFloats + 2 * kH + h * kD + d], num);
         den = fmaf(wt, merge[w * kMergeFloats + kH + h], den);
       }
-      if (NEW && has_new) {
+      if (has_new) {
         const float wt = __builtin_amdgcn_exp2f(newp[h] - big);
         num = fmaf(wt, newp[kH + d], num);
         den += wt;
@@ -677,9 +677,9 @@ __device__ __forceinline__ void combine_unit(const DecodeArgs &a, uint8_t *smem,
 // token is the band's last row, stored by the combining split; the first
 // split to count in stores its codes (step_encode.h).
 // TBF: the transforms are stored as bf16 (NOVA_KV_BF16_TRANSFORMS).
-// NEW: without a band, the step's token is encoded by other workgroups.
+// NEW: a step whose token other workgroups encode (step_encode.h).
 // Workgroup wg of n_wg.
-template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, bool NEW>
+template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF, int NEW>
 __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, const int wg, const int n_wg) {
   const int tid = threadIdx.x;
   // each XCD takes a contiguous range of the logical workgroup order
@@ -696,7 +696,7 @@ __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, co
   const int t0 = lo + split * a.chunk;  // splits tile the span read from the pools
   // the split that holds the new token (the last position attended) reads the
   // pools up to it
-  const bool has_new = NEW && S > 0 && split == (S - 1 - lo) / a.chunk;
+  const bool has_new = NEW == step::kNewCodes && S > 0 && split == (S - 1 - lo) / a.chunk;
   const int t1 = min(has_new ? S - 1 : tend, lo + (split + 1) * a.chunk);
   const size_t row0 = static_cast<size_t>(b) * a.num_q_heads + kv * G;
   const bool active = t0 < t1 || has_new;
@@ -771,31 +771,36 @@ __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, co
     }
     if (a.n_split > 1 && ctl[0] == 0) return;
   }
-  combine_unit<WAVES, BSTEP, TBF>(a, smem, b, kv, row0, split, active, S, lo, tend, att_lo, spn.sink_end, tv);
+  combine_unit<WAVES, BSTEP || NEW == step::kNewBand, TBF>(a, smem, b, kv, row0, split, active, S, lo, tend, att_lo, spn.sink_end, tv);
 }
 
 template <int WAVES, bool KS, bool FP8, bool SQ, bool BSTEP, bool TBF>
 __global__ void __launch_bounds__(WAVES * 64) decode_lut_d64(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES>()];
-  unit_pass<WAVES, KS, FP8, SQ, BSTEP, TBF, false>(a, smem, blockIdx.x, gridDim.x);
+  unit_pass<WAVES, KS, FP8, SQ, BSTEP, TBF, step::kNewNone>(a, smem, blockIdx.x, gridDim.x);
 }
 
-// The step without a band, its encoder in workgroups 0 .. n_enc - 1 (a multiple
-// of 8, so the other workgroups keep their XCDs).
-template <int WAVES, bool KS, bool FP8, bool SQ, bool TBF>
+// The step with its encoder in n_enc workgroups of the launch: without a band
+// the first ones (a multiple of 8, so the others keep their XCDs), which a
+// decoding workgroup may wait for; with one the last ones.
+template <int WAVES, bool KS, bool FP8, bool SQ, bool TBF, bool BAND>
 __global__ void __launch_bounds__(WAVES * 64) step_lut_d64(DecodeArgs a) {
   __shared__ __attribute__((aligned(16))) uint8_t smem[lds_bytes<WAVES>()];
   constexpr int TEAMS = WAVES / 4;
-  static_assert(TEAMS * sizeof(step::Scratch<kD>) + 4 * TEAMS <= lds_bytes<WAVES>(), "team scratch");
-  if (static_cast<int>(blockIdx.x) < a.n_enc) {
+  static_assert(TEAMS * (sizeof(step::Scratch<kD>) + step::kWide + 4) <= lds_bytes<WAVES>(), "team scratch");
+  const int n_main = static_cast<int>(gridDim.x) - a.n_enc;
+  const int wg = static_cast<int>(blockIdx.x);
+  if (BAND ? wg >= n_main : wg < a.n_enc) {
     const int bsz = a.layout.block_size;
     const int bs_shift = (bsz & (bsz - 1)) == 0 ? __builtin_ctz(bsz) : -1;
-    step::encode_workgroup<kD, TEAMS, KS, FP8, SQ, TBF>(a, smem, blockIdx.x, [&](const int b, const int kv, const int p) {
-      return subtile_offset(a, b, kv, p & ~15, bs_shift) + static_cast<size_t>(p & 15) * kL;
-    });
+    step::encode_workgroup<kD, TEAMS, KS, FP8, SQ, TBF, !BAND>(
+        a, smem, BAND ? wg - n_main : wg, [&](const int b, const int kv, const int p) {
+          return subtile_offset(a, b, kv, p & ~15, bs_shift) + static_cast<size_t>(p & 15) * kL;
+        });
     return;
   }
-  unit_pass<WAVES, KS, FP8, SQ, false, TBF, true>(a, smem, blockIdx.x - a.n_enc, gridDim.x - a.n_enc);
+  unit_pass<WAVES, KS, FP8, SQ, false, TBF, BAND ? step::kNewBand : step::kNewCodes>(
+      a, smem, BAND ? wg : wg - a.n_enc, n_main);
 }
 
 }  // namespace
@@ -819,31 +824,33 @@ void launch_d64(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStrea
   }
 }
 
+template <bool KS, bool SQ, bool TBF>
+void launch_step_format_d64(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStream_t stream) {
+  constexpr int W = 16;
+  if (a.band_k)
+    a.cb_fp8 ? step_lut_d64<W, KS, true, SQ, TBF, true><<<grid, block, 0, stream>>>(a)
+             : step_lut_d64<W, KS, false, SQ, TBF, true><<<grid, block, 0, stream>>>(a);
+  else
+    a.cb_fp8 ? step_lut_d64<W, KS, true, SQ, TBF, false><<<grid, block, 0, stream>>>(a)
+             : step_lut_d64<W, KS, false, SQ, TBF, false><<<grid, block, 0, stream>>>(a);
+}
+
 template <bool TBF>
 void launch_step_d64(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStream_t stream) {
-  constexpr int W = 16;
-  if (a.v_sq) {
-    if (a.k_scales)
-      a.cb_fp8 ? step_lut_d64<W, true, true, true, TBF><<<grid, block, 0, stream>>>(a)
-               : step_lut_d64<W, true, false, true, TBF><<<grid, block, 0, stream>>>(a);
-    else
-      a.cb_fp8 ? step_lut_d64<W, false, true, true, TBF><<<grid, block, 0, stream>>>(a)
-               : step_lut_d64<W, false, false, true, TBF><<<grid, block, 0, stream>>>(a);
-  } else if (a.k_scales) {
-    a.cb_fp8 ? step_lut_d64<W, true, true, false, TBF><<<grid, block, 0, stream>>>(a)
-             : step_lut_d64<W, true, false, false, TBF><<<grid, block, 0, stream>>>(a);
-  } else {
-    a.cb_fp8 ? step_lut_d64<W, false, true, false, TBF><<<grid, block, 0, stream>>>(a)
-             : step_lut_d64<W, false, false, false, TBF><<<grid, block, 0, stream>>>(a);
-  }
+  if (a.v_sq)
+    a.k_scales ? launch_step_format_d64<true, true, TBF>(a, grid, block, stream)
+               : launch_step_format_d64<false, true, TBF>(a, grid, block, stream);
+  else
+    a.k_scales ? launch_step_format_d64<true, false, TBF>(a, grid, block, stream)
+               : launch_step_format_d64<false, false, TBF>(a, grid, block, stream);
 }
 
 hipError_t launch_decode_lut64(const DecodeArgs &a, hipStream_t stream) {
   // 16 waves, 4 per SIMD: the kernel fits in 128 VGPRs.  A step (append) runs
   // here only with a band whose recent part holds the new token.
-  // (its encoder then in the first split to arrive), or without one with
-  // encoder workgroups.
-  if (a.n_enc > 0 ? (!a.append || a.band_k || a.n_enc % 8 != 0) : (a.append && !(a.band_k && a.n_rec >= 1)))
+  // (its encoder then in the first split to arrive), or with encoder workgroups.
+  if (a.n_enc > 0 ? (!a.append || a.n_enc % 8 != 0 || (a.band_k && a.n_rec < 1))
+                  : (a.append && !(a.band_k && a.n_rec >= 1)))
     return hipErrorInvalidValue;
   const dim3 grid(static_cast<unsigned>(a.batch * a.num_kv_heads * a.n_split + a.n_enc));
   const dim3 block(16 * 64);

@@ -181,6 +181,48 @@ __device__ __forceinline__ void token_coefficients(const int t, Scratch<D> &s, c
   }
 }
 
+// All D coefficients of one token (x in xs) into u[D] with every transform row
+// requested at once, for a team with registers and LDS to spare: thread t sums
+// D / RG rows of columns 4 c4 .. 4 c4 + 3, and the RG row groups' partials (part,
+// 8 KB) are added in order.  Two meetings of the team (sync).
+template <int D>
+struct WideRows {
+  static constexpr int C4 = D / 4, RG = kTeam / C4, RPT = D / RG;
+};
+template <int D>
+__device__ __forceinline__ void load_wide_rows(const int t, const void *tm, const int tbf, T4 (&rows)[WideRows<D>::RPT]) {
+  using W = WideRows<D>;
+#pragma unroll
+  for (int j = 0; j < W::RPT; ++j)
+    rows[j] = load_t4(tm, static_cast<size_t>(W::RPT * (t / W::C4) + j) * D + 4 * (t % W::C4), tbf);
+}
+template <int D, class Sync>
+__device__ __forceinline__ void wide_coefficients(const int t, const double *xs, const int tbf,
+                                                  const T4 (&rows)[WideRows<D>::RPT], double *part, double *u, Sync sync) {
+  using W = WideRows<D>;
+  const int rg = t / W::C4, c4 = t % W::C4;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int j = 0; j < W::RPT; ++j) {
+    const double x = xs[W::RPT * rg + j];
+    const float4 tr = t4_value(rows[j], tbf);
+    acc[0] = fma(x, static_cast<double>(tr.x), acc[0]);
+    acc[1] = fma(x, static_cast<double>(tr.y), acc[1]);
+    acc[2] = fma(x, static_cast<double>(tr.z), acc[2]);
+    acc[3] = fma(x, static_cast<double>(tr.w), acc[3]);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) part[rg * D + 4 * c4 + i] = acc[i];
+  sync();
+  if (t < D) {
+    double v = part[t];
+#pragma unroll
+    for (int r = 1; r < W::RG; ++r) v += part[r * D + t];
+    u[t] = v;
+  }
+  sync();
+}
+
 // Scalar value arm of one token (paper: Sec. "Bit rate" and the
 // implementation table: per-token affine INT2 values with a BF16 scale and
 // offset) from its D coefficients u: offset = bf16(min), scale =

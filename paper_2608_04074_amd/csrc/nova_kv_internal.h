@@ -77,10 +77,10 @@ struct DecodeArgs {
   uint8_t *k_codes_w, *v_codes_w;  // the pools k_codes / v_codes, written at the new position
   uint16_t *k_scales_w, *v_sq_w;   // the key-scale and scalar-arm pools, written there (else nullptr)
   uint16_t *band_k_w, *band_v_w;   // the band buffers, written at the new token's slot (else nullptr)
-  // Fused step without a band, on a launch that leaves CUs idle: workgroups
-  // 0 .. n_enc - 1 encode (enc_per_unit per unit; step_encode.h), the others
-  // decode, and the split that holds position seq_lens[b] - 1 takes that
-  // token from xnew.  n_enc = 0: the splits' encoder teams do it.
+  // Fused step: n_enc workgroups encode (enc_per_unit per unit; step_encode.h),
+  // the others decode, and without a band the split that holds position
+  // seq_lens[b] - 1 takes that token from xnew.  n_enc = 0: the splits' encoder
+  // teams do it.
   int n_enc, enc_per_unit;
   // Tagged exchange of the head_dim-128 table kernel (64-bit words, the tag
   // in the high half): split partials [B*Hkv][n_split][kXchSlotWords] and

@@ -75,10 +75,14 @@ struct NoPublish {
 // of the pools, by team thread t (0..255); meet() is the team's meeting, and
 // publish(word, value) gets every stored value.
 // TBF: the transforms are stored as bf16.
+// wide: 8 KB of LDS for whole-token tasks that request the transform at once
+// (encoder workgroups; nullptr: block after block, in the registers that a
+// decoding workgroup leaves).
 template <int D, bool KS, bool SQ, bool TBF, class Meet, class Publish = NoPublish>
 __device__ __forceinline__ void encode_token(const DecodeArgs &a, Scratch<D> &ls, const int b, const int kv,
                                              const int first, const int stride, const size_t tokoff, const int t,
-                                             const bool fp8, Meet meet, Publish publish = NoPublish()) {
+                                             const bool fp8, Meet meet, Publish publish = NoPublish(),
+                                             double *wide = nullptr) {
   using T = Tasks<D, KS, SQ>;
   constexpr int L = D / kGroupDim;
   const size_t elem = (static_cast<size_t>(b) * a.num_kv_heads + kv) * D + (t & (D - 1));
@@ -100,11 +104,20 @@ __device__ __forceinline__ void encode_token(const DecodeArgs &a, Scratch<D> &ls
     T4 rows[D / 32];
     uint2 cw[encblk::kPer];
     if ((key && KS) || (!key && SQ)) {
-      encblk::load_rows<D>(t, tm, TBF, 0, rows);
-      if (key) encblk::load_codewords(t, cb, fp8, cw0, 0, cw);
-      if (t < D) s.xs[t] = element(key);
-      meet();
-      encblk::token_coefficients<D>(t, s, tm, TBF, rows, u, meet);
+      if (wide) {
+        T4 all[encblk::WideRows<D>::RPT];
+        encblk::load_wide_rows<D>(t, tm, TBF, all);
+        if (key) encblk::load_codewords(t, cb, fp8, cw0, 0, cw);
+        if (t < D) s.xs[t] = element(key);
+        meet();
+        encblk::wide_coefficients<D>(t, s.xs, TBF, all, wide, u, meet);
+      } else {
+        encblk::load_rows<D>(t, tm, TBF, 0, rows);
+        if (key) encblk::load_codewords(t, cb, fp8, cw0, 0, cw);
+        if (t < D) s.xs[t] = element(key);
+        meet();
+        encblk::token_coefficients<D>(t, s, tm, TBF, rows, u, meet);
+      }
       if (key) {
         // rho, then the blocks' codes of the coefficients divided by it (the
         // next block's codewords requested while one block is searched)
@@ -191,15 +204,22 @@ __device__ __forceinline__ void store_band_rows(const DecodeArgs &a, const int b
 
 // ---- the step's encode in workgroups of its own
 //
-// Without a band, where a launch leaves CUs idle, the step's token is encoded
-// by workgroups of the same launch that do nothing else: workgroups 0 ..
-// n_enc - 1, enc_per_unit for each (sequence, KV head), each with TEAMS teams.
-// They hand the token's values to the split that holds its position as tagged
-// words, while that split is still in its setup or token loop.  They come
-// first in the dispatch order, so they run whatever waits for them.
+// Where the step's launch leaves CUs idle, n_enc workgroups of it do nothing
+// else than encode its token: enc_per_unit for each (sequence, KV head), each
+// with TEAMS teams.
+//  * Without a band they hand the token's values to the split that holds its
+//    position as tagged words (HAND), while that split is still in its setup
+//    or token loop.  They come first in the dispatch order, so they run
+//    whatever waits for them.
+//  * With the token in the band nothing waits for them, and they come last.
+//    (In a full launch they would follow the decode: 32 sequences of 8192
+//    tokens in the deployed format took 75 us so, 63 in two launches.)
+constexpr int kNewNone = 0, kNewCodes = 1, kNewBand = 2;  // what a decoding workgroup does about the token
 
-// An encoder workgroup's work (workgroup wg < n_enc).
-template <int D, int TEAMS, bool KS, bool FP8, bool SQ, bool TBF, class RowOf>
+constexpr int kWide = 8192;  // LDS bytes of a team's whole-token sums
+
+// An encoder workgroup's work (number wg < n_enc).
+template <int D, int TEAMS, bool KS, bool FP8, bool SQ, bool TBF, bool HAND, class RowOf>
 __device__ __forceinline__ void encode_workgroup(const DecodeArgs &a, uint8_t *smem, const int wg, RowOf row_of) {
   const int unit = wg / a.enc_per_unit, e = wg - unit * a.enc_per_unit;
   if (unit >= a.batch * a.num_kv_heads) return;  // n_enc is rounded up
@@ -208,15 +228,18 @@ __device__ __forceinline__ void encode_workgroup(const DecodeArgs &a, uint8_t *s
   if (S <= 0) return;
   const int tid = threadIdx.x, team = tid >> 8;
   Scratch<D> *ls = reinterpret_cast<Scratch<D> *>(smem);
-  int *ctr = reinterpret_cast<int *>(smem + TEAMS * sizeof(Scratch<D>));
+  double *wide = reinterpret_cast<double *>(smem + TEAMS * sizeof(Scratch<D>));
+  int *ctr = reinterpret_cast<int *>(smem + TEAMS * (sizeof(Scratch<D>) + kWide));
   if (tid < TEAMS) ctr[tid] = 0;
   __syncthreads();
   uint64_t *xn = a.xnew + static_cast<size_t>(unit) * 8 * 32;
   int phase = 0;  // shared by every copy of the meeting
   auto meet = [&] { team_meet(ctr + team, ++phase); };
-  auto publish = [&](const int w, const uint32_t v) { lut::put_word(a.epoch, xn + w, __uint_as_float(v)); };
+  auto publish = [&](const int w, const uint32_t v) {
+    if constexpr (HAND) lut::put_word(a.epoch, xn + w, __uint_as_float(v));
+  };
   encode_token<D, KS, SQ, TBF>(a, ls[team], b, kv, e * TEAMS + team, TEAMS * a.enc_per_unit, row_of(b, kv, S - 1),
-                               tid & 255, FP8, meet, publish);
+                               tid & 255, FP8, meet, publish, wide + team * (kWide / 8));
 }
 
 // The handed-over words of a unit's new token, read by one whole wave: lane l
