@@ -301,6 +301,206 @@ __device__ int search_exact(const void *cb, const size_t cw, const int lane, con
   return arg;
 }
 
+// Stages 1 and 2 of the search of one group: the code of each token (one per
+// lane; NB 32-token tiles), and whether it has to be searched in fp64 (flag).
+// raw: codewords 4 lane .. +3 as loaded; stage, arow: the wave's staging and
+// the lane's operand rows in it; us: the token's coefficients, exact up to fp32
+// rounding, or each within err of its value (APPROX).
+template <bool FP8, int NB, bool APPROX = false>
+__device__ __forceinline__ int score_group(const uint2 (&raw)[4], uint8_t *stage, const uint8_t *arow, const int lane,
+                                           float (&us)[4], const float err, bool &flag) {
+  const uint32_t half = lane >> 5;
+  // codewords: the group's scale, its scaled codewords and norms into LDS
+  uint2 w[4];
+  uint32_t big = 0u;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    w[j] = codeword_f16(raw[j], FP8);
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    const u16x2 ax = __builtin_bit_cast(u16x2, w[j].x & 0x7fff7fffu), ay = __builtin_bit_cast(u16x2, w[j].y & 0x7fff7fffu);
+    big = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, big), __builtin_elementwise_max(ax, ay)));
+  }
+  big = wave_max_u32(max(big & 0xffffu, big >> 16));
+  // exponent of the largest coordinate (fp16 bits; denormals count as 2^-24 ..)
+  const float cmaxf = half_bits_to_float(static_cast<uint16_t>(big));
+  const int ec = big == 0u ? 0 : __builtin_amdgcn_frexp_expf(cmaxf) - 1;
+  {
+    const int e = 5 - ec, e1 = max(min(e, 14), -14), e2 = e - e1;  // e in [-10, 29]
+    const _Float16 f1 = static_cast<_Float16>(ldexpf(1.f, e1)), f2 = static_cast<_Float16>(ldexpf(1.f, e2));
+    const f16x2 s1 = {f1, f1}, s2 = {f2, f2};
+    asm volatile("" ::: "memory");  // the group before is read; a wave's LDS operations run in order
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint2 c = make_uint2(scale_f16x2(w[j].x, s1, s2), scale_f16x2(w[j].y, s1, s2));
+      const f16x2 cx = __builtin_bit_cast(f16x2, c.x), cy = __builtin_bit_cast(f16x2, c.y);
+      const float c0 = cx[0], c1 = cx[1], c2 = cy[0], c3 = cy[1];
+      float n = fmaf(c3, c3, fmaf(c2, c2, fmaf(c1, c1, c0 * c0)));
+      asm volatile("" : "+v"(n));  // hi is f16 of the rounded n everywhere (no product fused into the conversion)
+      const _Float16 hi = static_cast<_Float16>(n);
+      const _Float16 lo = static_cast<_Float16>(n - static_cast<float>(hi));
+      reinterpret_cast<uint2 *>(stage)[4 * lane + j] = c;
+      reinterpret_cast<uint2 *>(stage + 2048)[4 * lane + j] = make_uint2(pack_f16(hi, lo), 0x00003c00u);
+    }
+    asm volatile("" ::: "memory");
+  }
+
+  // token operand: w = -2 u scaled to below 128, as hi and lo; f weighs the
+  // norms, o makes the scores about squared distances
+  float ws[4], f, o, a2;
+  int eu;
+  {
+    const float um = fmaxf(fmaxf(fabsf(us[0]), fabsf(us[1])), fmaxf(fabsf(us[2]), fabsf(us[3])));
+    eu = max(um > 0.f ? __builtin_amdgcn_frexp_expf(um) - 1 : ec, ec);
+    flag = eu - ec > 14 || big >= 0x7c00u;  // f below fp16's normal range, or a codeword that is not finite
+    a2 = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      us[i] = ldexpf(us[i], 5 - eu);
+      a2 = fmaf(us[i], us[i], a2);
+      ws[i] = -2.f * us[i];
+    }
+    f = ldexpf(1.f, max(ec - eu, -14));
+    a2 = ldexpf(a2, min(eu - ec, 64));
+    o = static_cast<float>(static_cast<_Float16>(fminf(a2, 16384.f)));
+  }
+  uint32_t b0[4], b1[4];  // B operands of the token tiles: lanes 0..31 {hi, lo} of w, lanes 32..63 {f, f, o, 0 ..}
+  {
+    _Float16 hi[4], lo[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      hi[i] = static_cast<_Float16>(ws[i]);
+      lo[i] = static_cast<_Float16>(ws[i] - static_cast<float>(hi[i]));
+    }
+    const uint32_t x[4] = {pack_f16(hi[0], hi[1]), pack_f16(hi[2], hi[3]), pack_f16(lo[0], lo[1]), pack_f16(lo[2], lo[3])};
+    const _Float16 fh = static_cast<_Float16>(f);
+    const uint32_t y[4] = {pack_f16(fh, fh), pack_f16(static_cast<_Float16>(o), static_cast<_Float16>(0.f)), 0u, 0u};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const auto s = __builtin_amdgcn_permlane32_swap(x[i], y[i], false, false);
+      b0[i] = s[0];
+      b1[i] = s[1];
+    }
+  }
+  const f16x8 bv0 = __builtin_bit_cast(f16x8, make_uint4(b0[0], b0[1], b0[2], b0[3]));
+  const f16x8 bv1 = __builtin_bit_cast(f16x8, make_uint4(b1[0], b1[1], b1[2], b1[3]));
+
+  // ---- 1: block minima.  The low 5 bits of a block's minimum hold the block
+  // (its first codeword / 8): 4 t + b here, bit 1 (the lane half) below.
+  float best[NB], second[NB];
+#pragma unroll
+  for (int c = 0; c < NB; ++c) best[c] = second[c] = INFINITY;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    const uint2 av = *reinterpret_cast<const uint2 *>(arow + 256 * t);
+    const f16x8 aop = __builtin_bit_cast(f16x8, make_uint4(av.x, av.y, half ? 0u : av.x, half ? 0u : av.y));
+    const float16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float16_t d[NB];
+    d[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, bv0, zero, 0, 0, 0);
+    if constexpr (NB == 2) d[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, bv1, zero, 0, 0, 0);
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        const float *v = reinterpret_cast<const float *>(&d[c]) + 8 * b;
+        float mn = fminf(fminf(v[0], v[1]), v[2]);
+        mn = fminf(fminf(mn, v[3]), v[4]);
+        mn = fminf(fminf(mn, v[5]), v[6]);
+        mn = fminf(mn, v[7]);
+        const float key = __uint_as_float((__float_as_uint(mn) & 0xffffffe0u) | static_cast<uint32_t>(4 * t + b));
+        second[c] = __builtin_amdgcn_fmed3f(best[c], second[c], key);
+        best[c] = fminf(best[c], key);
+      }
+  }
+  // both lane halves of each tile; lane = token
+  float kb, sb;
+  {
+#pragma unroll
+    for (int c = 0; c < NB; ++c) best[c] = __uint_as_float(__float_as_uint(best[c]) | (half << 1));
+    const float bl = best[0], bh = NB == 2 ? best[NB - 1] : best[0];
+    const float sl = second[0], sh = NB == 2 ? second[NB - 1] : second[0];
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bl), __float_as_uint(bh), false, false);
+    const auto s2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(sl), __float_as_uint(sh), false, false);
+    const uint32_t x0 = sw[0], x1 = sw[1], y0 = s2[0], y1 = s2[1];
+    const float p0 = __uint_as_float(x0), p1 = __uint_as_float(x1);
+    kb = fminf(p0, p1);
+    sb = fminf(fminf(fmaxf(p0, p1), __uint_as_float(y0)), __uint_as_float(y1));
+  }
+  const uint32_t blk = __float_as_uint(kb) & 31u;
+
+  // ---- 2: the block's 8 scores in fp32
+  float v1 = INFINITY, v2 = INFINITY;
+  {
+    const uint8_t *cp = stage + 64 * blk, *np = stage + 2048 + 64 * blk;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      const uint4 c = reinterpret_cast<const uint4 *>(cp)[p], n = reinterpret_cast<const uint4 *>(np)[p];
+      const uint32_t cw[2][2] = {{c.x, c.y}, {c.z, c.w}}, nn[2] = {n.x, n.z};
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const f16x2 cx = __builtin_bit_cast(f16x2, cw[e][0]), cy = __builtin_bit_cast(f16x2, cw[e][1]);
+        const f16x2 nx = __builtin_bit_cast(f16x2, nn[e]);
+        float sc = fmaf(static_cast<float>(nx[0]), f, o);
+        sc = fmaf(static_cast<float>(nx[1]), f, sc);
+        sc = fmaf(static_cast<float>(cx[0]), ws[0], sc);
+        sc = fmaf(static_cast<float>(cx[1]), ws[1], sc);
+        sc = fmaf(static_cast<float>(cy[0]), ws[2], sc);
+        sc = fmaf(static_cast<float>(cy[1]), ws[3], sc);
+        const float key = __uint_as_float((__float_as_uint(sc) & 0xfffffff8u) | static_cast<uint32_t>(2 * p + e));
+        v2 = __builtin_amdgcn_fmed3f(v1, v2, key);
+        v1 = fminf(v1, key);
+      }
+    }
+  }
+  const float next = fminf(sb, v2), gap = next - v1;
+  float bound = 0x1p-16f * (2.f * a2 + fabsf(v1)) + 0x1p-14f;
+  if constexpr (APPROX) {
+    // two scores differ by 2 (c1 - c2) . u: an error of E in each coordinate
+    // moves their gap by at most 4 E (|u - c1| + |u - c2| + 4 E), the
+    // distances about the runner-up's where the gap is small
+    const float es = err * __builtin_amdgcn_exp2f(0.5f * static_cast<float>(10 - ec - eu));
+    bound += 8.f * es * (__builtin_amdgcn_sqrtf(fmaxf(next + (a2 - o), 0.f)) + 2.f * es);
+  }
+  flag = flag || !(gap > bound);
+  return static_cast<int>(8 * blk + (__float_as_uint(v1) & 7u));
+}
+
+// The inputs of a tile: NK vectors of four elements (index(k): the first one's
+// index), as fp32 bits.  Every load is issued before the first is used: 8- or
+// 16-byte loads where the inputs' address allows them, single elements
+// otherwise.
+template <int NK, class Index>
+__device__ __forceinline__ void load_inputs(const EncodeArgs &a, const void *src, uint4 (&x)[NK], Index index) {
+  if (a.in_bf16) {
+    const uint16_t *p = static_cast<const uint16_t *>(src);
+    uint2 h[NK];
+    if (a.in_vec) {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) h[k] = *reinterpret_cast<const uint2 *>(p + index(k));
+    } else {
+      uint16_t e[NK][4];
+#pragma unroll
+      for (int k = 0; k < NK; ++k)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) e[k][i] = p[index(k) + i];
+#pragma unroll
+      for (int k = 0; k < NK; ++k)
+        h[k] = make_uint2(e[k][0] | (static_cast<uint32_t>(e[k][1]) << 16), e[k][2] | (static_cast<uint32_t>(e[k][3]) << 16));
+    }
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+      x[k] = make_uint4(h[k].x << 16, h[k].x & 0xffff0000u, h[k].y << 16, h[k].y & 0xffff0000u);
+  } else if (a.in_vec) {
+#pragma unroll
+    for (int k = 0; k < NK; ++k) x[k] = *reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(src) + index(k));
+  } else {
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const uint32_t *p = static_cast<const uint32_t *>(src) + index(k);
+      x[k] = make_uint4(p[0], p[1], p[2], p[3]);
+    }
+  }
+}
+
 // NTT: 16-token tiles per wave (2 or 4).  SPLIT: a workgroup searches a quarter
 // of the groups (blockIdx.z >> 1 says which), one per wave, for launches whose
 // tiles alone leave the chip idle.  It forms only the quarter's coefficients:
@@ -308,14 +508,14 @@ __device__ int search_exact(const void *cb, const size_t cw, const int lane, con
 // A scaled key needs them all: there every workgroup runs the whole transform
 // and wave ot searches group 4 ot + quarter.
 template <int D, bool FP8, bool TBF, int NTT, bool SPLIT>
-__global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
+__global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a, const int first_side) {
   using T_ = TileShape<D, NTT>;
   constexpr int L = D / kGroupDim, NT = 64 * kTileWaves, TOK = T_::TOKENS, RS = T_::RS, KS = D / 4;
   constexpr int BYTES = T_::bytes(SPLIT);
   __shared__ __attribute__((aligned(16))) uint8_t smem[BYTES];
   double *xs = reinterpret_cast<double *>(smem);
 
-  const int kv = blockIdx.y, side = blockIdx.z & 1;
+  const int kv = blockIdx.y, side = first_side + (blockIdx.z & 1);
   const int only = SPLIT ? static_cast<int>(blockIdx.z >> 1) : 0;
   const bool scalar_arm = side == 1 && a.v_sq;
   if (SPLIT && scalar_arm && only != 0) return;  // its levels need every coefficient: one workgroup
@@ -354,47 +554,16 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
   const int tok_p0 = a.start_pos[tok_b];
 
   // inputs (minus k_bar for keys) to LDS in fp64: thread tid stages four
-  // coordinates of tokens tid / (D / 4) + k * TP.  Every load is issued before
-  // the first is used: 8- or 16-byte loads where the inputs' address allows
-  // them, single elements otherwise.
+  // coordinates of tokens tid / (D / 4) + k * TP
   {
     constexpr int C4 = D / 4, TP = NT / C4, NK = TOK / TP;
     static_assert(NT % C4 == 0 && TOK % TP == 0, "a thread stages four coordinates of NK tokens");
     const int d = 4 * (tid % C4), s0 = tid / C4;
     const float4 kb = side == 0 ? *reinterpret_cast<const float4 *>(a.kbar + kv * D + d) : make_float4(0.f, 0.f, 0.f, 0.f);
     uint4 x[NK];  // fp32 bits
-    auto index = [&](const int k) {  // past the last token the last one is read again
+    load_inputs<NK>(a, src, x, [&](const int k) {  // past the last token the last one is read again
       return (static_cast<size_t>(min(n0 + s0 + k * TP, n_tok - 1)) * a.num_kv_heads + kv) * D + d;
-    };
-    if (a.in_bf16) {
-      const uint16_t *p = static_cast<const uint16_t *>(src);
-      uint2 h[NK];
-      if (a.in_vec) {
-#pragma unroll
-        for (int k = 0; k < NK; ++k) h[k] = *reinterpret_cast<const uint2 *>(p + index(k));
-      } else {
-        uint16_t e[NK][4];
-#pragma unroll
-        for (int k = 0; k < NK; ++k)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) e[k][i] = p[index(k) + i];
-#pragma unroll
-        for (int k = 0; k < NK; ++k)
-          h[k] = make_uint2(e[k][0] | (static_cast<uint32_t>(e[k][1]) << 16), e[k][2] | (static_cast<uint32_t>(e[k][3]) << 16));
-      }
-#pragma unroll
-      for (int k = 0; k < NK; ++k)
-        x[k] = make_uint4(h[k].x << 16, h[k].x & 0xffff0000u, h[k].y << 16, h[k].y & 0xffff0000u);
-    } else if (a.in_vec) {
-#pragma unroll
-      for (int k = 0; k < NK; ++k) x[k] = *reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(src) + index(k));
-    } else {
-#pragma unroll
-      for (int k = 0; k < NK; ++k) {
-        const uint32_t *p = static_cast<const uint32_t *>(src) + index(k);
-        x[k] = make_uint4(p[0], p[1], p[2], p[3]);
-      }
-    }
+    });
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
       double *row = xs + (s0 + k * TP) * RS + d;
@@ -593,160 +762,17 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
       transpose_rows(u);  // u[i]: coordinate i of token `lane`
     }
 
-    // codewords: the group's scale, its scaled codewords and norms into LDS
-    uint2 w[4];
-    uint32_t big = 0u;
+    bool flag;
+    float us[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      w[j] = codeword_f16(rn[j], FP8);
-      typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-      const u16x2 ax = __builtin_bit_cast(u16x2, w[j].x & 0x7fff7fffu), ay = __builtin_bit_cast(u16x2, w[j].y & 0x7fff7fffu);
-      big = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, big), __builtin_elementwise_max(ax, ay)));
-    }
+    for (int i = 0; i < 4; ++i) us[i] = static_cast<float>(u[i]);
+    const uint2 cur[4] = {rn[0], rn[1], rn[2], rn[3]};
     if (k + 1 < (SPLIT ? 1 : 4)) {
 #pragma unroll
       for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
     }
-    big = wave_max_u32(max(big & 0xffffu, big >> 16));
-    // exponent of the largest coordinate (fp16 bits; denormals count as 2^-24 ..)
-    const float cmaxf = half_bits_to_float(static_cast<uint16_t>(big));
-    const int ec = big == 0u ? 0 : __builtin_amdgcn_frexp_expf(cmaxf) - 1;
-    {
-      const int e = 5 - ec, e1 = max(min(e, 14), -14), e2 = e - e1;  // e in [-10, 29]
-      const _Float16 f1 = static_cast<_Float16>(ldexpf(1.f, e1)), f2 = static_cast<_Float16>(ldexpf(1.f, e2));
-      const f16x2 s1 = {f1, f1}, s2 = {f2, f2};
-      asm volatile("" ::: "memory");  // the group before is read; a wave's LDS operations run in order
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint2 c = make_uint2(scale_f16x2(w[j].x, s1, s2), scale_f16x2(w[j].y, s1, s2));
-        const f16x2 cx = __builtin_bit_cast(f16x2, c.x), cy = __builtin_bit_cast(f16x2, c.y);
-        const float c0 = cx[0], c1 = cx[1], c2 = cy[0], c3 = cy[1];
-        float n = fmaf(c3, c3, fmaf(c2, c2, fmaf(c1, c1, c0 * c0)));
-        asm volatile("" : "+v"(n));  // hi is f16 of the rounded n everywhere (no product fused into the conversion)
-        const _Float16 hi = static_cast<_Float16>(n);
-        const _Float16 lo = static_cast<_Float16>(n - static_cast<float>(hi));
-        reinterpret_cast<uint2 *>(stage)[4 * lane + j] = c;
-        reinterpret_cast<uint2 *>(stage + 2048)[4 * lane + j] = make_uint2(pack_f16(hi, lo), 0x00003c00u);
-      }
-      asm volatile("" ::: "memory");
-    }
-
-    // token operand: w = -2 u scaled to below 128, as hi and lo; f weighs the
-    // norms, o makes the scores about squared distances
-    float ws[4], f, o, a2;
-    bool flag;
-    {
-      float us[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) us[i] = static_cast<float>(u[i]);
-      const float um = fmaxf(fmaxf(fabsf(us[0]), fabsf(us[1])), fmaxf(fabsf(us[2]), fabsf(us[3])));
-      const int eu = max(um > 0.f ? __builtin_amdgcn_frexp_expf(um) - 1 : ec, ec);
-      flag = eu - ec > 14 || big >= 0x7c00u;  // f below fp16's normal range, or a codeword that is not finite
-      a2 = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        us[i] = ldexpf(us[i], 5 - eu);
-        a2 = fmaf(us[i], us[i], a2);
-        ws[i] = -2.f * us[i];
-      }
-      f = ldexpf(1.f, max(ec - eu, -14));
-      a2 = ldexpf(a2, min(eu - ec, 64));
-      o = static_cast<float>(static_cast<_Float16>(fminf(a2, 16384.f)));
-    }
-    uint32_t b0[4], b1[4];  // B operands of the token tiles: lanes 0..31 {hi, lo} of w, lanes 32..63 {f, f, o, 0 ..}
-    {
-      _Float16 hi[4], lo[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        hi[i] = static_cast<_Float16>(ws[i]);
-        lo[i] = static_cast<_Float16>(ws[i] - static_cast<float>(hi[i]));
-      }
-      const uint32_t x[4] = {pack_f16(hi[0], hi[1]), pack_f16(hi[2], hi[3]), pack_f16(lo[0], lo[1]), pack_f16(lo[2], lo[3])};
-      const _Float16 fh = static_cast<_Float16>(f);
-      const uint32_t y[4] = {pack_f16(fh, fh), pack_f16(static_cast<_Float16>(o), static_cast<_Float16>(0.f)), 0u, 0u};
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const auto s = __builtin_amdgcn_permlane32_swap(x[i], y[i], false, false);
-        b0[i] = s[0];
-        b1[i] = s[1];
-      }
-    }
-    const f16x8 bv0 = __builtin_bit_cast(f16x8, make_uint4(b0[0], b0[1], b0[2], b0[3]));
-    const f16x8 bv1 = __builtin_bit_cast(f16x8, make_uint4(b1[0], b1[1], b1[2], b1[3]));
-
-    // ---- 1: block minima.  The low 5 bits of a block's minimum hold the block
-    // (its first codeword / 8): 4 t + b here, bit 1 (the lane half) below.
-    constexpr int NB = NTT == 4 ? 2 : 1;  // 32-token tiles
-    float best[NB], second[NB];
-#pragma unroll
-    for (int c = 0; c < NB; ++c) best[c] = second[c] = INFINITY;
-#pragma unroll
-    for (int t = 0; t < 8; ++t) {
-      const uint2 av = *reinterpret_cast<const uint2 *>(arow + 256 * t);
-      const f16x8 aop = __builtin_bit_cast(f16x8, make_uint4(av.x, av.y, half ? 0u : av.x, half ? 0u : av.y));
-      const float16_t zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-      float16_t d[NB];
-      d[0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, bv0, zero, 0, 0, 0);
-      if constexpr (NB == 2) d[1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, bv1, zero, 0, 0, 0);
-#pragma unroll
-      for (int c = 0; c < NB; ++c)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const float *v = reinterpret_cast<const float *>(&d[c]) + 8 * b;
-          float mn = fminf(fminf(v[0], v[1]), v[2]);
-          mn = fminf(fminf(mn, v[3]), v[4]);
-          mn = fminf(fminf(mn, v[5]), v[6]);
-          mn = fminf(mn, v[7]);
-          const float key = __uint_as_float((__float_as_uint(mn) & 0xffffffe0u) | static_cast<uint32_t>(4 * t + b));
-          second[c] = __builtin_amdgcn_fmed3f(best[c], second[c], key);
-          best[c] = fminf(best[c], key);
-        }
-    }
-    // both lane halves of each tile; lane = token
-    float kb, sb;
-    {
-#pragma unroll
-      for (int c = 0; c < NB; ++c) best[c] = __uint_as_float(__float_as_uint(best[c]) | (half << 1));
-      const float bl = best[0], bh = NB == 2 ? best[NB - 1] : best[0];
-      const float sl = second[0], sh = NB == 2 ? second[NB - 1] : second[0];
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(bl), __float_as_uint(bh), false, false);
-      const auto s2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(sl), __float_as_uint(sh), false, false);
-      const uint32_t x0 = sw[0], x1 = sw[1], y0 = s2[0], y1 = s2[1];
-      const float p0 = __uint_as_float(x0), p1 = __uint_as_float(x1);
-      kb = fminf(p0, p1);
-      sb = fminf(fminf(fmaxf(p0, p1), __uint_as_float(y0)), __uint_as_float(y1));
-    }
-    const uint32_t blk = __float_as_uint(kb) & 31u;
-
-    // ---- 2: the block's 8 scores in fp32
-    float v1 = INFINITY, v2 = INFINITY;
-    {
-      const uint8_t *cp = stage + 64 * blk, *np = stage + 2048 + 64 * blk;
-#pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        const uint4 c = reinterpret_cast<const uint4 *>(cp)[p], n = reinterpret_cast<const uint4 *>(np)[p];
-        const uint32_t cw[2][2] = {{c.x, c.y}, {c.z, c.w}}, nn[2] = {n.x, n.z};
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const f16x2 cx = __builtin_bit_cast(f16x2, cw[e][0]), cy = __builtin_bit_cast(f16x2, cw[e][1]);
-          const f16x2 nx = __builtin_bit_cast(f16x2, nn[e]);
-          float sc = fmaf(static_cast<float>(nx[0]), f, o);
-          sc = fmaf(static_cast<float>(nx[1]), f, sc);
-          sc = fmaf(static_cast<float>(cx[0]), ws[0], sc);
-          sc = fmaf(static_cast<float>(cx[1]), ws[1], sc);
-          sc = fmaf(static_cast<float>(cy[0]), ws[2], sc);
-          sc = fmaf(static_cast<float>(cy[1]), ws[3], sc);
-          const float key = __uint_as_float((__float_as_uint(sc) & 0xfffffff8u) | static_cast<uint32_t>(2 * p + e));
-          v2 = __builtin_amdgcn_fmed3f(v1, v2, key);
-          v1 = fminf(v1, key);
-        }
-      }
-    }
-    int code = static_cast<int>(8 * blk + (__float_as_uint(v1) & 7u));
-    // ---- 3: too close to call: the token's group in fp64
-    const float gap = fminf(sb, v2) - v1;
-    const float bound = 0x1p-16f * (2.f * a2 + fabsf(v1)) + 0x1p-14f;
-    flag = (flag || !(gap > bound)) && lane < 16 * NTT;
+    int code = score_group<FP8, NTT == 4 ? 2 : 1>(cur, stage, arow, lane, us, 0.f, flag);
+    flag = flag && lane < 16 * NTT;
     for (unsigned long long todo = __ballot(flag); todo; todo &= todo - 1) {
       const int l = __builtin_ctzll(todo);
       const double uu[4] = {readlane_f64(u[0], l), readlane_f64(u[1], l), readlane_f64(u[2], l), readlane_f64(u[3], l)};
@@ -763,6 +789,264 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a) {
   }
 }
 
+// v[t] of lane row q becomes v[q] of lane row t (32-bit words).
+__device__ __forceinline__ void swap16_f32(float &x, float &y) {
+  const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const uint32_t a = s[0], b = s[1];
+  x = __uint_as_float(a);
+  y = __uint_as_float(b);
+}
+__device__ __forceinline__ void swap32_f32(float &x, float &y) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  const uint32_t a = s[0], b = s[1];
+  x = __uint_as_float(a);
+  y = __uint_as_float(b);
+}
+__device__ __forceinline__ double wave_sum_f64(double x) {
+  x += row_dpp<0xB1>(x);
+  x += row_dpp<0x4E>(x);
+  x += row_dpp<0x141>(x);
+  x += row_dpp<0x140>(x);
+  double y = x;
+  swap_rows<16>(x, y);
+  x += y;
+  y = x;
+  swap_rows<32>(x, y);
+  return x + y;
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(const float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+
+// The tiled encoder of a plain side (no key scale, no scalar arm), for launches
+// that fill the chip: encode_tile's search on coefficients from the fp16 matrix
+// cores.
+//  * Transform: each token (minus k_bar, fp32) and the wave's 16 columns of T are
+//    scaled by powers of two and split into hi = f16(x), lo = f16(x - hi); the
+//    small products lo hi + hi lo are summed first, then hi hi, by
+//    v_mfma_f32_16x16x32_f16.  Each coefficient is then within
+//    E = 2^-18.5 |x| |T_j| of its value: an MFMA errs by at most 2^-21 of its
+//    terms and its accumulator (2^-23.5 measured), four of them with sums up to
+//    |x| |T_j|, 2^-19 together; the splits and the dropped lo lo add 2^-21.
+//  * Search: as in encode_tile, the test of the runner-up widened by what E can
+//    move a gap (score_group); a token that fails it has its group's four
+//    coefficients formed and searched in fp64 (one of 10^3 token-groups), so
+//    the codes are those of the fp64 transform.
+// The fp64 transform took 32 of about 70 cycles per token and group on a SIMD,
+// this one takes 3.
+template <int D, bool FP8, bool TBF>
+__global__ void __launch_bounds__(64 * kTileWaves) encode_fast(EncodeArgs a, const int first_side) {
+  using T_ = TileShape<D, 4>;
+  constexpr int L = D / kGroupDim, NT = 64 * kTileWaves, NTT = 4, TOK = T_::TOKENS;
+  constexpr int RH = D + 8;                         // LDS row stride of the split inputs (halves)
+  constexpr uint32_t kLo = TOK * RH * 2, kPlanes = 2 * kLo;
+  constexpr uint32_t kTok = kPlanes > T_::BYTES_SEARCH ? kPlanes : T_::BYTES_SEARCH;  // per token: exponent, norm
+  constexpr int KS = D / 32;                        // contraction steps of 32
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kTok + TOK * 8];
+  const int kv = blockIdx.y, side = first_side + blockIdx.z;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_tok = a.batch * a.n_new;
+  const int n0 = blockIdx.x * TOK;
+  const void *tm = transform_of(side == 0 ? a.t_k : a.t_v, kv, D, TBF);
+  const void *cb = side == 0 ? a.cb_k : a.cb_v;
+  const size_t cw0 = static_cast<size_t>(kv) * L * kCodebookSize;
+  const void *src = side == 0 ? a.k : a.v;
+  uint8_t *pool = side == 0 ? a.k_codes : a.v_codes;
+  const int m = lane & 15, q = lane >> 4;
+  const int ot = wave % T_::OT, th = wave / T_::OT;
+
+  // ---- columns of T: rows 32 ks + 8 q + e, column 16 ot + m
+  uint32_t tr[KS][8];
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+    for (int e = 0; e < 8; ++e) tr[ks][e] = load_t1_raw(tm, (32 * ks + 8 * q + e) * D + 16 * ot + m, TBF);
+
+  // the token that this lane stores (as in encode_tile)
+  const int tok = 16 * NTT * th + lane;
+  bool stored = n0 + tok < n_tok;
+  const int tok_b = stored ? (n0 + tok) / a.n_new : 0, tok_t = n0 + tok - tok_b * a.n_new;
+  const int tok_p0 = a.start_pos[tok_b];
+
+  // ---- inputs: thread tid takes four coordinates of tokens tid / (D / 4) + k TP
+  {
+    constexpr int C4 = D / 4, TP = NT / C4, NK = TOK / TP;
+    const int d = 4 * (tid % C4), s0 = tid / C4;
+    const float4 kb = side == 0 ? *reinterpret_cast<const float4 *>(a.kbar + kv * D + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+    uint4 x[NK];  // fp32 bits
+    load_inputs<NK>(a, src, x, [&](const int k) {
+      return (static_cast<size_t>(min(n0 + s0 + k * TP, n_tok - 1)) * a.num_kv_heads + kv) * D + d;
+    });
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const int t = s0 + k * TP;
+      float v[4] = {__uint_as_float(x[k].x) - kb.x, __uint_as_float(x[k].y) - kb.y, __uint_as_float(x[k].z) - kb.z,
+                    __uint_as_float(x[k].w) - kb.w};
+      if (n0 + t >= n_tok) v[0] = v[1] = v[2] = v[3] = 0.f;
+      // the token's largest element and its norm, over the C4 lanes that hold it
+      float big = fmaxf(fmaxf(fabsf(v[0]), fabsf(v[1])), fmaxf(fabsf(v[2]), fabsf(v[3])));
+      big = fmaxf(big, dpp_f32<0xB1>(big));
+      big = fmaxf(big, dpp_f32<0x4E>(big));
+      big = fmaxf(big, dpp_f32<0x141>(big));
+      big = fmaxf(big, dpp_f32<0x140>(big));
+      if constexpr (C4 == 32) {
+        float y = big;
+        swap16_f32(big, y);
+        big = fmaxf(big, y);
+      }
+      const int ex = big > 0.f ? __builtin_amdgcn_frexp_expf(big) : 0;
+      float n2 = 0.f;
+      _Float16 hi[4], lo[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float y = ldexpf(v[i], 5 - ex);
+        n2 = fmaf(y, y, n2);
+        hi[i] = static_cast<_Float16>(y);
+        lo[i] = static_cast<_Float16>(y - static_cast<float>(hi[i]));
+      }
+      n2 += dpp_f32<0xB1>(n2);
+      n2 += dpp_f32<0x4E>(n2);
+      n2 += dpp_f32<0x141>(n2);
+      n2 += dpp_f32<0x140>(n2);
+      if constexpr (C4 == 32) {
+        float y = n2;
+        swap16_f32(n2, y);
+        n2 += y;
+      }
+      uint8_t *row = smem + 2 * (t * RH + d);
+      *reinterpret_cast<uint2 *>(row) = make_uint2(pack_f16(hi[0], hi[1]), pack_f16(hi[2], hi[3]));
+      *reinterpret_cast<uint2 *>(row + kLo) = make_uint2(pack_f16(lo[0], lo[1]), pack_f16(lo[2], lo[3]));
+      if (d == 0)
+        *reinterpret_cast<uint2 *>(smem + kTok + 8 * t) =
+            make_uint2(static_cast<uint32_t>(ex), __float_as_uint(ldexpf(__builtin_amdgcn_sqrtf(n2), ex - 5)));
+      if (a.band_k && n0 + t < n_tok) {
+        const int b = (n0 + t) / a.n_new, p0 = a.start_pos[b] + a.start_offset;
+        store_band4(a, side, b, kv, p0 + n0 + t - b * a.n_new, p0 + a.n_new, d, x[k]);
+      }
+    }
+  }
+  // ---- T split, with the wave's scale and its largest column norm
+  f16x8 thi[KS], tlo[KS];
+  float tnorm;
+  int et;
+  {
+    float big = 0.f, n2 = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) big = fmaxf(big, fabsf(t1_raw_value(tr[ks][e], TBF)));
+    big = __uint_as_float(wave_max_u32(__float_as_uint(big)));
+    et = big > 0.f ? __builtin_amdgcn_frexp_expf(big) : 0;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float y = ldexpf(t1_raw_value(tr[ks][e], TBF), 5 - et);
+        n2 = fmaf(y, y, n2);
+        const _Float16 hi = static_cast<_Float16>(y);
+        thi[ks][e] = hi;
+        tlo[ks][e] = static_cast<_Float16>(y - static_cast<float>(hi));
+      }
+    float y = n2;  // over the lane rows, then the largest column
+    swap16_f32(n2, y);
+    n2 = y = n2 + y;
+    swap32_f32(n2, y);
+    n2 += y;
+    tnorm = ldexpf(__builtin_amdgcn_sqrtf(__uint_as_float(wave_max_u32(__float_as_uint(n2)))), et - 5);
+  }
+  __syncthreads();
+  const int tok_pos = tok_p0 + a.start_offset + tok_t;
+  stored = stored && position_in_pool(a.layout, tok_pos);
+  const int tok_blk = stored ? tok_pos / a.layout.block_size : 0;
+  int tok_phys = tok_b * a.layout.blocks_per_seq + tok_blk;
+  if (a.layout.block_table) tok_phys = a.layout.block_table[tok_phys];
+
+  // uf[k][i]: coordinate i of group 4 ot + k, token `lane`
+  float uf[4][4];
+#pragma unroll
+  for (int j = 0; j < NTT; ++j) {
+    typedef float float4_t __attribute__((ext_vector_type(4)));
+    f16x8 xh[KS], xl[KS];
+    const uint8_t *row = smem + 2 * ((16 * NTT * th + 16 * j + m) * RH + 8 * q);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      xh[ks] = *reinterpret_cast<const f16x8 *>(row + 64 * ks);
+      xl[ks] = *reinterpret_cast<const f16x8 *>(row + kLo + 64 * ks);
+    }
+    float4_t d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(tlo[ks], xh[ks], d, 0, 0, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(thi[ks], xl[ks], d, 0, 0, 0);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(thi[ks], xh[ks], d, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) uf[j][i] = d[i];  // lane (q, m): coordinate i of group q, token 16 j + m
+  }
+  const uint2 tinfo = *reinterpret_cast<const uint2 *>(smem + kTok + 8 * tok);
+  const int eu = static_cast<int>(tinfo.x) + et - 10;
+  const float err = 0x1.6a09e6p-19f * __uint_as_float(tinfo.y) * tnorm;  // 2^-18.5 |x| |T_j|
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    swap16_f32(uf[0][i], uf[1][i]);
+    swap16_f32(uf[2][i], uf[3][i]);
+    swap32_f32(uf[0][i], uf[2][i]);
+    swap32_f32(uf[1][i], uf[3][i]);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) uf[k][i] = ldexpf(uf[k][i], eu);
+  }
+  __syncthreads();  // every wave has read the inputs; the region is the search's
+  const size_t off = ((static_cast<size_t>(tok_phys) * a.num_kv_heads + kv) * a.layout.block_size +
+                      (tok_pos - tok_blk * a.layout.block_size)) * L;
+
+  uint8_t *stage = smem + kSelPart + wave * 4096;
+  const int r = lane & 31;
+  const uint8_t *arow = stage + 2048 * (lane >> 5) + 8 * (16 * ((r >> 2) & 1) + 4 * (r >> 3) + (r & 3));
+  const int g0 = 4 * ot;
+  uint2 rn[4];
+  auto group_cw = [&](const int k) { return cw0 + static_cast<size_t>(g0 + k) * kCodebookSize; };
+#pragma unroll
+  for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(0) + 4 * lane + j);
+  uint32_t code_acc = 0u;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const uint2 cur[4] = {rn[0], rn[1], rn[2], rn[3]};
+    if (k < 3) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
+    }
+    bool flag;
+    int code = score_group<FP8, 2, true>(cur, stage, arow, lane, uf[k], err, flag);
+    flag = flag && n0 + tok < n_tok;
+    for (unsigned long long todo = __ballot(flag); todo; todo &= todo - 1) {
+      // the token's four coefficients in fp64: a lane adds D / 64 rows
+      const int l = __builtin_ctzll(todo);
+      const size_t idx = (static_cast<size_t>(n0 + 16 * NTT * th + l) * a.num_kv_heads + kv) * D;
+      double uu[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < D / 64; ++i) {
+        const int row = lane + 64 * i;
+        double x = a.in_bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(src)[idx + row]))
+                             : static_cast<double>(static_cast<const float *>(src)[idx + row]);
+        if (side == 0) x -= static_cast<double>(a.kbar[kv * D + row]);
+        const float4 t = t4_value(load_t4(tm, static_cast<size_t>(row) * D + 4 * (g0 + k), TBF), TBF);
+        uu[0] = fma(x, static_cast<double>(t.x), uu[0]);
+        uu[1] = fma(x, static_cast<double>(t.y), uu[1]);
+        uu[2] = fma(x, static_cast<double>(t.z), uu[2]);
+        uu[3] = fma(x, static_cast<double>(t.w), uu[3]);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) uu[i] = wave_sum_f64(uu[i]);
+      const int c = search_exact<FP8>(cb, group_cw(k), lane, uu);
+      if (lane == l) code = c;
+    }
+    code_acc = (code_acc >> 8) | (static_cast<uint32_t>(code) << 24);
+  }
+  if (stored) *reinterpret_cast<uint32_t *>(pool + off + g0) = code_acc;
+}
+
 // TBF: the transforms are stored as bf16 (a compile-time choice, so that the
 // fp32 kernels carry no branch on it).
 // Whole groups per wave once the tiles give every CU a workgroup; below that one
@@ -773,12 +1057,22 @@ template <int D, bool FP8, bool TBF>
 void launch_tiles(const EncodeArgs &a, hipStream_t stream) {
   const long long n = static_cast<long long>(a.batch) * a.n_new;
   auto blocks = [&](const int tokens) { return static_cast<unsigned>((n + tokens - 1) / tokens); };
-  if (static_cast<long long>(blocks(TileShape<D, 4>::TOKENS)) * 2 * a.num_kv_heads >= 256)
-    encode_tile<D, FP8, TBF, 4, false>
-        <<<dim3(blocks(TileShape<D, 4>::TOKENS), a.num_kv_heads, 2), dim3(64 * kTileWaves), 0, stream>>>(a);
-  else
+  const dim3 block(64 * kTileWaves);
+  const unsigned tiles = blocks(TileShape<D, 4>::TOKENS);
+  if (static_cast<long long>(tiles) * 2 * a.num_kv_heads < 256) {
     encode_tile<D, FP8, TBF, 2, true>
-        <<<dim3(blocks(TileShape<D, 2>::TOKENS), a.num_kv_heads, 8), dim3(64 * kTileWaves), 0, stream>>>(a);
+        <<<dim3(blocks(TileShape<D, 2>::TOKENS), a.num_kv_heads, 8), block, 0, stream>>>(a, 0);
+    return;
+  }
+  // a scaled key and the scalar arm store values of the coefficients themselves
+  // and take the fp64 transform; the other sides encode_fast
+  const bool slow_k = a.k_scales, slow_v = a.v_sq;
+  if (!slow_k || !slow_v)
+    encode_fast<D, FP8, TBF>
+        <<<dim3(tiles, a.num_kv_heads, slow_k == slow_v ? 2 : 1), block, 0, stream>>>(a, slow_k ? 1 : 0);
+  if (slow_k || slow_v)
+    encode_tile<D, FP8, TBF, 4, false>
+        <<<dim3(tiles, a.num_kv_heads, slow_k == slow_v ? 2 : 1), block, 0, stream>>>(a, slow_k ? 0 : 1);
 }
 
 // Few tokens in the plain formats: encode_small, a workgroup per token, side and
