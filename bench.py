@@ -42,8 +42,8 @@ DECODE_KERNEL = "decode_lut_d128"
 # The step kernel's source and the headers it includes: a change to any of
 # them invalidates the committed counter summary.
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2608_04074_amd", "csrc", f)
-                  for f in ("decode_lut.hip", "band_attention.h", "encode_block.h", "lut_common.h",
-                            "nova_kv_internal.h")]
+                  for f in ("decode_lut.hip", "decode_lut_d128.h", "band_attention.h", "encode_block.h", "lut_common.h",
+                            "step_encode.h", "nova_kv_internal.h")]
 TRAFFIC_SUMMARY = os.path.join(ROOT, "profiles", "decode_lut_d128_qwen3_8b_traffic.md")
 COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "decode_lut_d128_qwen3_8b_counters.md")
 COPY_CALIB_BYTES = 256 << 20

@@ -15,7 +15,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libnovakv.so")
-SOURCES = ["api.hip", "decode.hip", "decode_lut.hip", "decode_lut64.hip", "decode_vq.hip", "encode.hip", "host_checks.cpp"]
+SOURCES = ["api.hip", "decode.hip", "decode_lut.hip", "decode_lut64.hip", "step_lut.hip", "step_lut64.hip",
+           "decode_vq.hip", "encode.hip", "host_checks.cpp"]
 ARCH = "gfx950"
 
 HIPCC_FLAGS = [

@@ -191,6 +191,9 @@ int plan_group_size(int n_split);
 bool lut_path_eligible(int head_dim, int gqa, int block_size);
 hipError_t launch_decode_lut(const DecodeArgs &a, hipStream_t stream);    // head_dim 128
 hipError_t launch_decode_lut64(const DecodeArgs &a, hipStream_t stream);  // head_dim 64
+// The same kernels as a step with encoder workgroups (the two above launch them).
+hipError_t launch_step_lut(const DecodeArgs &a, dim3 grid, dim3 block, hipStream_t stream);
+hipError_t launch_step_lut64(const DecodeArgs &a, dim3 grid, dim3 block, hipStream_t stream);
 // Everything else: up to kMaxGqa query heads per KV head, any block size.
 hipError_t launch_decode_vq(const DecodeArgs &a, hipStream_t stream);
 hipError_t launch_encode(const EncodeArgs &a, hipStream_t stream);
