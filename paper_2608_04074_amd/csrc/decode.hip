@@ -98,10 +98,10 @@ Splits plan_splits(const SplitCost &c, const int units, const int span, const in
 }
 // head_dim 128: 2.7 ns a token and CU, 12.5 us a round; head_dim 64: 1.9 ns and 12
 // us, decode_vq: 4 ns and 16 us, both with splits that wait for their stores
-// (0.35 and 0.7 us each in the combine).
+// (0.35 and 0.4 us each in the combine).
 constexpr SplitCost kCost128 = {4600, 30, 650, 1700, 4000, 900, 1100, 2500, 3, 12 * 64, 7},
                     kCost64 = {6300, 180, 0, 2400, 5700, 1200, 0, 0, 4, 16 * 64, 0},
-                    kCostVq = {4000, 170, 0, 0, 0, 0, 0, 0, 0, 0, 3};
+                    kCostVq = {4000, 100, 0, 0, 0, 0, 0, 0, 0, 0, 3};
 
 }  // namespace
 

@@ -128,3 +128,24 @@ def test_against_oracle(nk, D, gqa, bs, fmt, window, band, use_sink):
                                           sq_v=(s2[:, 0], s2[:, 1]) if sq else None)
     assert not out[0].any()
     assert_outputs_close(out.reshape(-1, D), ref.reshape(-1, D), tol=TOL32, what=f"decode_vq D={D} gqa={gqa} {bs} {fmt}")
+
+
+@pytest.mark.parametrize("n", [7001, 20011, 60001])
+def test_combine_of_many_splits(nk, n):
+    """One KV head over up to 40 splits, which the combine reads eight at a
+    time; the second sequence leaves all but the first of them empty."""
+    B, H, gqa, D, L = 2, 1, 8, 128, 32
+    wl = synth.get_workload("qwen3_8b").scaled(num_kv_heads=H, num_q_heads=gqa)
+    arr = dict(synth.bench_params(wl))
+    P = nk.NovaKVParams.from_arrays(arr)
+    rng = np.random.default_rng(n)
+    codes = rng.integers(0, 256, (2, B, n, L), dtype=np.uint8)
+    q = rng.standard_normal((B, gqa, D)).astype(np.float32)
+    lens = np.array([n, 129], np.int32)
+    print(f"[gpu-case] decode_vq many splits n={n}", flush=True)
+    out = nk.decode_attn(P, nk.CacheLayout.contiguous(n), dev(q, torch.float32), dev(codes[0][:, None], torch.uint8),
+                         dev(codes[1][:, None], torch.uint8), dev(lens, torch.int32), n).cpu().numpy()
+    hp = oatt.head_params(arr, 0)
+    ref = np.stack([oatt.decode_rows(q[b].astype(np.float64), codes[0, b, :m], codes[1, b, :m], hp, 1 / np.sqrt(D), 0, None)
+                    for b, m in enumerate(lens)])
+    assert_outputs_close(out.reshape(-1, D), ref.reshape(-1, D), tol=TOL32, what=f"decode_vq of {n} tokens")
