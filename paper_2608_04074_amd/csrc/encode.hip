@@ -301,16 +301,15 @@ __device__ int search_exact(const void *cb, const size_t cw, const int lane, con
   return arg;
 }
 
-// Stages 1 and 2 of the search of one group: the code of each token (one per
-// lane; NB 32-token tiles), and whether it has to be searched in fp64 (flag).
-// raw: codewords 4 lane .. +3 as loaded; stage, arow: the wave's staging and
-// the lane's operand rows in it; us: the token's coefficients, exact up to fp32
-// rounding, or each within err of its value (APPROX).
-template <bool FP8, int NB, bool APPROX = false>
-__device__ __forceinline__ int score_group(const uint2 (&raw)[4], uint8_t *stage, const uint8_t *arow, const int lane,
-                                           float (&us)[4], const float err, bool &flag) {
-  const uint32_t half = lane >> 5;
-  // codewords: the group's scale, its scaled codewords and norms into LDS
+// Exponent of a group's largest coordinate (fp16 bits; denormals count as 2^-24 ..).
+__device__ __forceinline__ int group_exponent(const uint32_t big) {
+  return big == 0u ? 0 : __builtin_amdgcn_frexp_expf(half_bits_to_float(static_cast<uint16_t>(big))) - 1;
+}
+
+// Codewords 4 lane .. +3 of a group, as loaded (raw): scaled, with their norms,
+// into the wave's staging.  Returns the largest magnitude's fp16 bits.
+template <bool FP8>
+__device__ __forceinline__ uint32_t stage_group(const uint2 (&raw)[4], uint8_t *stage, const int lane) {
   uint2 w[4];
   uint32_t big = 0u;
 #pragma unroll
@@ -321,9 +320,7 @@ __device__ __forceinline__ int score_group(const uint2 (&raw)[4], uint8_t *stage
     big = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, big), __builtin_elementwise_max(ax, ay)));
   }
   big = wave_max_u32(max(big & 0xffffu, big >> 16));
-  // exponent of the largest coordinate (fp16 bits; denormals count as 2^-24 ..)
-  const float cmaxf = half_bits_to_float(static_cast<uint16_t>(big));
-  const int ec = big == 0u ? 0 : __builtin_amdgcn_frexp_expf(cmaxf) - 1;
+  const int ec = group_exponent(big);
   {
     const int e = 5 - ec, e1 = max(min(e, 14), -14), e2 = e - e1;  // e in [-10, 29]
     const _Float16 f1 = static_cast<_Float16>(ldexpf(1.f, e1)), f2 = static_cast<_Float16>(ldexpf(1.f, e2));
@@ -343,7 +340,19 @@ __device__ __forceinline__ int score_group(const uint2 (&raw)[4], uint8_t *stage
     }
     asm volatile("" ::: "memory");
   }
+  return big;
+}
 
+// Stages 1 and 2 of the search of a staged group: the code of each token (one
+// per lane; NB 32-token tiles), and whether it has to be searched in fp64 (flag).
+// big: stage_group's result; stage, arow: the wave's staging and the lane's
+// operand rows in it; us: the token's coefficients, exact up to fp32 rounding,
+// or each within err of its value (APPROX).
+template <int NB, bool APPROX = false>
+__device__ __forceinline__ int score_group(const uint32_t big, const uint8_t *stage, const uint8_t *arow, const int lane,
+                                           float (&us)[4], const float err, bool &flag) {
+  const uint32_t half = lane >> 5;
+  const int ec = group_exponent(big);
   // token operand: w = -2 u scaled to below 128, as hi and lo; f weighs the
   // norms, o makes the scores about squared distances
   float ws[4], f, o, a2;
@@ -771,7 +780,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a, con
 #pragma unroll
       for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
     }
-    int code = score_group<FP8, NTT == 4 ? 2 : 1>(cur, stage, arow, lane, us, 0.f, flag);
+    int code = score_group<NTT == 4 ? 2 : 1>(stage_group<FP8>(cur, stage, lane), stage, arow, lane, us, 0.f, flag);
     flag = flag && lane < 16 * NTT;
     for (unsigned long long todo = __ballot(flag); todo; todo &= todo - 1) {
       const int l = __builtin_ctzll(todo);
@@ -835,8 +844,15 @@ __device__ __forceinline__ float dpp_f32(const float x) {
 //    the codes are those of the fp64 transform.
 // The fp64 transform took 32 of about 70 cycles per token and group on a SIMD,
 // this one takes 3.
-template <int D, bool FP8, bool TBF>
-__global__ void __launch_bounds__(64 * kTileWaves) encode_fast(EncodeArgs a, const int first_side) {
+// A workgroup does NS tiles: T's split (25 of about 725 vector instructions per
+// token and group and lane in single tiles) and the staging of a group's
+// codewords (55) serve all of them.  One tile's coefficients are formed after
+// the other's in the same LDS, and scored one after the other, so that two
+// workgroups still share a CU (128 VGPRs, 42 KiB of LDS).  32 x 4096 tokens, 8 KV
+// heads of 128: 2111 us with the fp64 transform, 1508 with single tiles, 1445 in
+// pairs.
+template <int D, bool FP8, bool TBF, int NS>
+__global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, const int first_side) {
   using T_ = TileShape<D, 4>;
   constexpr int L = D / kGroupDim, NT = 64 * kTileWaves, NTT = 4, TOK = T_::TOKENS;
   constexpr int RH = D + 8;                         // LDS row stride of the split inputs (halves)
@@ -848,7 +864,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_fast(EncodeArgs a, con
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_tok = a.batch * a.n_new;
-  const int n0 = blockIdx.x * TOK;
+  const int first = blockIdx.x * TOK * NS;
   const void *tm = transform_of(side == 0 ? a.t_k : a.t_v, kv, D, TBF);
   const void *cb = side == 0 ? a.cb_k : a.cb_v;
   const size_t cw0 = static_cast<size_t>(kv) * L * kCodebookSize;
@@ -864,21 +880,30 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_fast(EncodeArgs a, con
 #pragma unroll
     for (int e = 0; e < 8; ++e) tr[ks][e] = load_t1_raw(tm, (32 * ks + 8 * q + e) * D + 16 * ot + m, TBF);
 
-  // the token that this lane stores (as in encode_tile)
-  const int tok = 16 * NTT * th + lane;
-  bool stored = n0 + tok < n_tok;
-  const int tok_b = stored ? (n0 + tok) / a.n_new : 0, tok_t = n0 + tok - tok_b * a.n_new;
-  const int tok_p0 = a.start_pos[tok_b];
-
   // ---- inputs: thread tid takes four coordinates of tokens tid / (D / 4) + k TP
-  {
-    constexpr int C4 = D / 4, TP = NT / C4, NK = TOK / TP;
-    const int d = 4 * (tid % C4), s0 = tid / C4;
-    const float4 kb = side == 0 ? *reinterpret_cast<const float4 *>(a.kbar + kv * D + d) : make_float4(0.f, 0.f, 0.f, 0.f);
+  constexpr int C4 = D / 4, TP = NT / C4, NK = TOK / TP;
+  const int d4 = 4 * (tid % C4), s0 = tid / C4;
+  const float4 kb = side == 0 ? *reinterpret_cast<const float4 *>(a.kbar + kv * D + d4) : make_float4(0.f, 0.f, 0.f, 0.f);
+  // the tokens that this lane stores (as in encode_tile)
+  const int tok = 16 * NTT * th + lane;
+  float uf[NS][4][4];  // [s][k][i]: coordinate i of group 4 ot + k, token `tok` of tile s
+  float err[NS];
+  size_t off[NS];
+  bool stored[NS];
+
+  f16x8 thi[KS], tlo[KS];  // T split, with the wave's scale and its largest column norm
+  float tnorm = 0.f;
+  int et = 0;
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int n0 = first + s * TOK;
     uint4 x[NK];  // fp32 bits
     load_inputs<NK>(a, src, x, [&](const int k) {
-      return (static_cast<size_t>(min(n0 + s0 + k * TP, n_tok - 1)) * a.num_kv_heads + kv) * D + d;
+      return (static_cast<size_t>(min(n0 + s0 + k * TP, n_tok - 1)) * a.num_kv_heads + kv) * D + d4;
     });
+    stored[s] = n0 + tok < n_tok;
+    const int tok_b = stored[s] ? (n0 + tok) / a.n_new : 0, tok_t = n0 + tok - tok_b * a.n_new;
+    const int tok_p0 = a.start_pos[tok_b];
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
       const int t = s0 + k * TP;
@@ -915,91 +940,85 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_fast(EncodeArgs a, con
         swap16_f32(n2, y);
         n2 += y;
       }
-      uint8_t *row = smem + 2 * (t * RH + d);
+      uint8_t *row = smem + 2 * (t * RH + d4);
       *reinterpret_cast<uint2 *>(row) = make_uint2(pack_f16(hi[0], hi[1]), pack_f16(hi[2], hi[3]));
       *reinterpret_cast<uint2 *>(row + kLo) = make_uint2(pack_f16(lo[0], lo[1]), pack_f16(lo[2], lo[3]));
-      if (d == 0)
+      if (d4 == 0)
         *reinterpret_cast<uint2 *>(smem + kTok + 8 * t) =
             make_uint2(static_cast<uint32_t>(ex), __float_as_uint(ldexpf(__builtin_amdgcn_sqrtf(n2), ex - 5)));
       if (a.band_k && n0 + t < n_tok) {
         const int b = (n0 + t) / a.n_new, p0 = a.start_pos[b] + a.start_offset;
-        store_band4(a, side, b, kv, p0 + n0 + t - b * a.n_new, p0 + a.n_new, d, x[k]);
+        store_band4(a, side, b, kv, p0 + n0 + t - b * a.n_new, p0 + a.n_new, d4, x[k]);
       }
     }
-  }
-  // ---- T split, with the wave's scale and its largest column norm
-  f16x8 thi[KS], tlo[KS];
-  float tnorm;
-  int et;
-  {
-    float big = 0.f, n2 = 0.f;
+    if (s == 0) {
+      float big = 0.f, n2 = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
+      for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) big = fmaxf(big, fabsf(t1_raw_value(tr[ks][e], TBF)));
-    big = __uint_as_float(wave_max_u32(__float_as_uint(big)));
-    et = big > 0.f ? __builtin_amdgcn_frexp_expf(big) : 0;
+        for (int e = 0; e < 8; ++e) big = fmaxf(big, fabsf(t1_raw_value(tr[ks][e], TBF)));
+      big = __uint_as_float(wave_max_u32(__float_as_uint(big)));
+      et = big > 0.f ? __builtin_amdgcn_frexp_expf(big) : 0;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
+      for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float y = ldexpf(t1_raw_value(tr[ks][e], TBF), 5 - et);
-        n2 = fmaf(y, y, n2);
-        const _Float16 hi = static_cast<_Float16>(y);
-        thi[ks][e] = hi;
-        tlo[ks][e] = static_cast<_Float16>(y - static_cast<float>(hi));
-      }
-    float y = n2;  // over the lane rows, then the largest column
-    swap16_f32(n2, y);
-    n2 = y = n2 + y;
-    swap32_f32(n2, y);
-    n2 += y;
-    tnorm = ldexpf(__builtin_amdgcn_sqrtf(__uint_as_float(wave_max_u32(__float_as_uint(n2)))), et - 5);
-  }
-  __syncthreads();
-  const int tok_pos = tok_p0 + a.start_offset + tok_t;
-  stored = stored && position_in_pool(a.layout, tok_pos);
-  const int tok_blk = stored ? tok_pos / a.layout.block_size : 0;
-  int tok_phys = tok_b * a.layout.blocks_per_seq + tok_blk;
-  if (a.layout.block_table) tok_phys = a.layout.block_table[tok_phys];
+        for (int e = 0; e < 8; ++e) {
+          const float y = ldexpf(t1_raw_value(tr[ks][e], TBF), 5 - et);
+          n2 = fmaf(y, y, n2);
+          const _Float16 hi = static_cast<_Float16>(y);
+          thi[ks][e] = hi;
+          tlo[ks][e] = static_cast<_Float16>(y - static_cast<float>(hi));
+        }
+      float y = n2;  // over the lane rows, then the largest column
+      swap16_f32(n2, y);
+      n2 = y = n2 + y;
+      swap32_f32(n2, y);
+      n2 += y;
+      tnorm = ldexpf(__builtin_amdgcn_sqrtf(__uint_as_float(wave_max_u32(__float_as_uint(n2)))), et - 5);
+    }
+    __syncthreads();
+    const int tok_pos = tok_p0 + a.start_offset + tok_t;
+    stored[s] = stored[s] && position_in_pool(a.layout, tok_pos);
+    const int tok_blk = stored[s] ? tok_pos / a.layout.block_size : 0;
+    int tok_phys = tok_b * a.layout.blocks_per_seq + tok_blk;
+    if (a.layout.block_table) tok_phys = a.layout.block_table[tok_phys];
 
-  // uf[k][i]: coordinate i of group 4 ot + k, token `lane`
-  float uf[4][4];
 #pragma unroll
-  for (int j = 0; j < NTT; ++j) {
-    typedef float float4_t __attribute__((ext_vector_type(4)));
-    f16x8 xh[KS], xl[KS];
-    const uint8_t *row = smem + 2 * ((16 * NTT * th + 16 * j + m) * RH + 8 * q);
+    for (int j = 0; j < NTT; ++j) {
+      typedef float float4_t __attribute__((ext_vector_type(4)));
+      f16x8 xh[KS], xl[KS];
+      const uint8_t *row = smem + 2 * ((16 * NTT * th + 16 * j + m) * RH + 8 * q);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      xh[ks] = *reinterpret_cast<const f16x8 *>(row + 64 * ks);
-      xl[ks] = *reinterpret_cast<const f16x8 *>(row + kLo + 64 * ks);
+      for (int ks = 0; ks < KS; ++ks) {
+        xh[ks] = *reinterpret_cast<const f16x8 *>(row + 64 * ks);
+        xl[ks] = *reinterpret_cast<const f16x8 *>(row + kLo + 64 * ks);
+      }
+      float4_t d = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(tlo[ks], xh[ks], d, 0, 0, 0);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(thi[ks], xl[ks], d, 0, 0, 0);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(thi[ks], xh[ks], d, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) uf[s][j][i] = d[i];  // lane (q, m): coordinate i of group q, token 16 j + m
     }
-    float4_t d = {0.f, 0.f, 0.f, 0.f};
+    const uint2 tinfo = *reinterpret_cast<const uint2 *>(smem + kTok + 8 * tok);
+    const int eu = static_cast<int>(tinfo.x) + et - 10;
+    err[s] = 0x1.6a09e6p-19f * __uint_as_float(tinfo.y) * tnorm;  // 2^-18.5 |x| |T_j|
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(tlo[ks], xh[ks], d, 0, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+      swap16_f32(uf[s][0][i], uf[s][1][i]);
+      swap16_f32(uf[s][2][i], uf[s][3][i]);
+      swap32_f32(uf[s][0][i], uf[s][2][i]);
+      swap32_f32(uf[s][1][i], uf[s][3][i]);
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(thi[ks], xl[ks], d, 0, 0, 0);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) d = __builtin_amdgcn_mfma_f32_16x16x32_f16(thi[ks], xh[ks], d, 0, 0, 0);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) uf[j][i] = d[i];  // lane (q, m): coordinate i of group q, token 16 j + m
+      for (int k = 0; k < 4; ++k) uf[s][k][i] = ldexpf(uf[s][k][i], eu);
+    }
+    __syncthreads();  // every wave has read the inputs; the region is the next tile's or the search's
+    off[s] = ((static_cast<size_t>(tok_phys) * a.num_kv_heads + kv) * a.layout.block_size +
+                (tok_pos - tok_blk * a.layout.block_size)) * L;
   }
-  const uint2 tinfo = *reinterpret_cast<const uint2 *>(smem + kTok + 8 * tok);
-  const int eu = static_cast<int>(tinfo.x) + et - 10;
-  const float err = 0x1.6a09e6p-19f * __uint_as_float(tinfo.y) * tnorm;  // 2^-18.5 |x| |T_j|
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    swap16_f32(uf[0][i], uf[1][i]);
-    swap16_f32(uf[2][i], uf[3][i]);
-    swap32_f32(uf[0][i], uf[2][i]);
-    swap32_f32(uf[1][i], uf[3][i]);
-#pragma unroll
-    for (int k = 0; k < 4; ++k) uf[k][i] = ldexpf(uf[k][i], eu);
-  }
-  __syncthreads();  // every wave has read the inputs; the region is the search's
-  const size_t off = ((static_cast<size_t>(tok_phys) * a.num_kv_heads + kv) * a.layout.block_size +
-                      (tok_pos - tok_blk * a.layout.block_size)) * L;
 
   uint8_t *stage = smem + kSelPart + wave * 4096;
   const int r = lane & 31;
@@ -1009,7 +1028,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_fast(EncodeArgs a, con
   auto group_cw = [&](const int k) { return cw0 + static_cast<size_t>(g0 + k) * kCodebookSize; };
 #pragma unroll
   for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(0) + 4 * lane + j);
-  uint32_t code_acc = 0u;
+  uint32_t code_acc[NS] = {};
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const uint2 cur[4] = {rn[0], rn[1], rn[2], rn[3]};
@@ -1017,35 +1036,50 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_fast(EncodeArgs a, con
 #pragma unroll
       for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
     }
-    bool flag;
-    int code = score_group<FP8, 2, true>(cur, stage, arow, lane, uf[k], err, flag);
-    flag = flag && n0 + tok < n_tok;
-    for (unsigned long long todo = __ballot(flag); todo; todo &= todo - 1) {
-      // the token's four coefficients in fp64: a lane adds D / 64 rows
-      const int l = __builtin_ctzll(todo);
-      const size_t idx = (static_cast<size_t>(n0 + 16 * NTT * th + l) * a.num_kv_heads + kv) * D;
-      double uu[4] = {0.0, 0.0, 0.0, 0.0};
+    const uint32_t big = stage_group<FP8>(cur, stage, lane);
 #pragma unroll
-      for (int i = 0; i < D / 64; ++i) {
-        const int row = lane + 64 * i;
-        double x = a.in_bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(src)[idx + row]))
-                             : static_cast<double>(static_cast<const float *>(src)[idx + row]);
-        if (side == 0) x -= static_cast<double>(a.kbar[kv * D + row]);
-        const float4 t = t4_value(load_t4(tm, static_cast<size_t>(row) * D + 4 * (g0 + k), TBF), TBF);
-        uu[0] = fma(x, static_cast<double>(t.x), uu[0]);
-        uu[1] = fma(x, static_cast<double>(t.y), uu[1]);
-        uu[2] = fma(x, static_cast<double>(t.z), uu[2]);
-        uu[3] = fma(x, static_cast<double>(t.w), uu[3]);
+    for (int s = 0; s < NS; ++s) {
+      const int n0 = first + s * TOK;
+      bool flag;
+      int code = score_group<2, true>(big, stage, arow, lane, uf[s][k], err[s], flag);
+      flag = flag && n0 + tok < n_tok;
+      for (unsigned long long todo = __ballot(flag); todo; todo &= todo - 1) {
+        // the token's four coefficients in fp64: a lane adds D / 64 rows
+        const int l = __builtin_ctzll(todo);
+        const size_t idx = (static_cast<size_t>(n0 + 16 * NTT * th + l) * a.num_kv_heads + kv) * D;
+        double uu[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < D / 64; ++i) {
+          const int row = lane + 64 * i;
+          double x = a.in_bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(src)[idx + row]))
+                               : static_cast<double>(static_cast<const float *>(src)[idx + row]);
+          if (side == 0) x -= static_cast<double>(a.kbar[kv * D + row]);
+          const float4 t = t4_value(load_t4(tm, static_cast<size_t>(row) * D + 4 * (g0 + k), TBF), TBF);
+          uu[0] = fma(x, static_cast<double>(t.x), uu[0]);
+          uu[1] = fma(x, static_cast<double>(t.y), uu[1]);
+          uu[2] = fma(x, static_cast<double>(t.z), uu[2]);
+          uu[3] = fma(x, static_cast<double>(t.w), uu[3]);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) uu[i] = wave_sum_f64(uu[i]);
+        const int c = search_exact<FP8>(cb, group_cw(k), lane, uu);
+        if (lane == l) code = c;
       }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) uu[i] = wave_sum_f64(uu[i]);
-      const int c = search_exact<FP8>(cb, group_cw(k), lane, uu);
-      if (lane == l) code = c;
+      code_acc[s] = (code_acc[s] >> 8) | (static_cast<uint32_t>(code) << 24);
+      __builtin_amdgcn_sched_barrier(0);  // one tile's scores in registers at a time
     }
-    code_acc = (code_acc >> 8) | (static_cast<uint32_t>(code) << 24);
   }
-  if (stored) *reinterpret_cast<uint32_t *>(pool + off + g0) = code_acc;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    if (stored[s]) *reinterpret_cast<uint32_t *>(pool + off[s] + g0) = code_acc[s];
 }
+
+// Two tiles per workgroup of encode_fast (its T split and its staged codewords
+// serve both) once that leaves two launch rounds of two workgroups per CU; below
+// that one tile, which ends sooner: 2 x 1024 tokens, 8 KV heads of 128, 34.6 us in
+// single tiles; 2 x 4096 tokens 116.4 us in single tiles and 112.7 in pairs, 32 x
+// 4096 1508 and 1445, 4 x 12000 of head_dim 64 275 and 252.
+constexpr int kPairWorkgroups = 1024;
 
 // TBF: the transforms are stored as bf16 (a compile-time choice, so that the
 // fp32 kernels carry no branch on it).
@@ -1067,9 +1101,14 @@ void launch_tiles(const EncodeArgs &a, hipStream_t stream) {
   // a scaled key and the scalar arm store values of the coefficients themselves
   // and take the fp64 transform; the other sides encode_fast
   const bool slow_k = a.k_scales, slow_v = a.v_sq;
-  if (!slow_k || !slow_v)
-    encode_fast<D, FP8, TBF>
-        <<<dim3(tiles, a.num_kv_heads, slow_k == slow_v ? 2 : 1), block, 0, stream>>>(a, slow_k ? 1 : 0);
+  if (!slow_k || !slow_v) {
+    const int sides = slow_k == slow_v ? 2 : 1;
+    const unsigned pairs = (tiles + 1) / 2;
+    if (static_cast<long long>(pairs) * sides * a.num_kv_heads >= kPairWorkgroups)
+      encode_fast<D, FP8, TBF, 2><<<dim3(pairs, a.num_kv_heads, sides), block, 0, stream>>>(a, slow_k ? 1 : 0);
+    else
+      encode_fast<D, FP8, TBF, 1><<<dim3(tiles, a.num_kv_heads, sides), block, 0, stream>>>(a, slow_k ? 1 : 0);
+  }
   if (slow_k || slow_v)
     encode_tile<D, FP8, TBF, 4, false>
         <<<dim3(tiles, a.num_kv_heads, slow_k == slow_v ? 2 : 1), block, 0, stream>>>(a, slow_k ? 0 : 1);

@@ -16,6 +16,7 @@ import synth
 from helpers import compare_codes
 from oracle import attention as oatt
 from oracle import codec as ocodec
+from oracle import fp8 as ofp8
 
 pytestmark = pytest.mark.gpu
 
@@ -72,3 +73,56 @@ def test_codes(nk, D, B, n_new, H, kind):
                 compare_codes(got_v, cv, gv, f"encode_tile D={D} {kind} b{b} kv{kv} V")
                 if kind == "ties":
                     assert not (got_k == 100).any() and not (got_v == 100).any()
+
+
+@pytest.mark.parametrize("D,B,n_new,fmt", [(128, 3, 2735, ""), (128, 3, 5466, "key_scale"), (64, 3, 5465, ""),
+                                           (64, 5, 3300, "fp8 bf16"), (128, 1, 8192, "f32")])
+def test_two_tiles_per_workgroup(nk, D, B, n_new, fmt):
+    """Launches large enough for workgroups of two tiles (the last of them with
+    an empty, a partial or a full second tile) store what calls of one sequence
+    or of a quarter of it store, which take a workgroup per tile; the oracle on
+    some tokens of them."""
+    H, L = 8, D // 4
+    wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=H, num_q_heads=H)
+    params = dict(synth.bench_params(wl))
+    arr, ks = dict(params), "key_scale" in fmt
+    if "fp8" in fmt:
+        for k in ("cb_k", "cb_v"):
+            arr[k] = ofp8.e4m3_bits(ofp8.snap_e4m3(arr[k].astype(np.float64)))
+            params[k] = ofp8.e4m3_value(arr[k])
+    if "bf16" in fmt:
+        for k in ("t_k", "t_k_inv_t", "t_v"):
+            params[k] = synth.round_to_bf16(arr[k])
+    P = nk.NovaKVParams.from_arrays(arr, key_scale=ks, bf16_transforms="bf16" in fmt)
+    rng = np.random.default_rng(n_new)
+    cap = n_new + 11
+    start = rng.integers(0, 12, B).astype(np.int32)
+    dt = torch.float32 if "f32" in fmt else torch.bfloat16
+    kk, vv = (torch.as_tensor(rng.standard_normal((B, n_new, H, D))).to(dt).cuda() for _ in range(2))
+    sp = dev(start, torch.int32)
+
+    def pools():
+        p = [torch.zeros((B, H, cap, L), dtype=torch.uint8, device="cuda") for _ in range(2)]
+        return p + ([torch.zeros((B, H, cap), dtype=torch.bfloat16, device="cuda")] if ks else [])
+
+    def encode(p, b0, b1, t0, t1):
+        p = [x[b0:b1] for x in p]
+        nk.encode(P, nk.CacheLayout.contiguous(cap), kk[b0:b1, t0:t1].contiguous(), vv[b0:b1, t0:t1].contiguous(),
+                  (sp[b0:b1] + t0).contiguous(), p[0], p[1], **(dict(k_scales=p[2]) if ks else {}))
+
+    print(f"[gpu-case] encode_fast, two tiles per workgroup, D={D} B={B} n_new={n_new} {fmt}", flush=True)
+    whole, parts = pools(), pools()
+    encode(whole, 0, B, 0, n_new)
+    for b in range(B):
+        for t0 in range(0, n_new, 2735):
+            encode(parts, b, b + 1, t0, min(n_new, t0 + 2735))
+    for w, p in zip(whole, parts):
+        assert torch.equal(w, p)
+    tail = slice(n_new - 30, n_new)
+    s0, kd, vd = int(start[B - 1]), kk[B - 1, tail].double().cpu().numpy(), vv[B - 1, tail].double().cpu().numpy()
+    for kv in (0, H - 1):
+        ck, gk, cv, gv = ocodec.encode_tokens(kd[:, kv], vd[:, kv], oatt.head_params(params, kv))
+        rows = slice(s0 + n_new - 30, s0 + n_new)
+        if not ks:
+            compare_codes(whole[0][B - 1, kv, rows].cpu().numpy(), ck, gk, f"encode_fast pairs D={D} kv{kv} K")
+        compare_codes(whole[1][B - 1, kv, rows].cpu().numpy(), cv, gv, f"encode_fast pairs D={D} kv{kv} V")
