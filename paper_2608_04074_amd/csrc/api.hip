@@ -338,6 +338,7 @@ nova_kv_status append_step(const nova_kv_params *p, const nova_kv_layout *layout
     if (plan.step == novakv::kStepWorkgroups) {
       a.enc_per_unit = plan.enc_per_unit;
       a.n_enc = (batch * p->num_kv_heads * plan.enc_per_unit + 7) & ~7;
+      a.new_polls = new_token_polls();
     }
     a.k_new = k_new;
     a.v_new = v_new;

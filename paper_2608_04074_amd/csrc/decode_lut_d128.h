@@ -790,7 +790,13 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     // the last wave, which has the fewest rounds of a short split
     if (has_new && wave == WAVES - 1) {
       uint32_t code = 0, scale = 0, sq = 0;
-      const bool ok = step::take_new_token<kL, KS, SQ>(a, b * a.num_kv_heads + kv, lane, code, scale, sq);
+      const bool there = step::take_new_token<kL, KS, SQ>(a, b * a.num_kv_heads + kv, lane, code, scale, sq);
+      if (__builtin_expect_with_probability(!there, 0, 0.99999)) {
+        const step::TokenValues t = step::form_new_token<kD, KS, FP8, SQ, TBF>(step::token_inputs<kD, TBF>(a, b, kv), lane);
+        code = t.code;
+        scale = t.scale;
+        sq = t.sq;
+      }
       const int g = lane & 31;
       half4_t e = {0, 0, 0, 0};
       if (lane < 32) e = *reinterpret_cast<const half4_t *>(smem + code * 256 + g * 8);
@@ -807,7 +813,6 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
           const float sc = __uint_as_float(sq << 16), of = __uint_as_float(sq & 0xffff0000u);
           v = make_float4(fmaf(sc, v.x, of), fmaf(sc, v.y, of), fmaf(sc, v.z, of), fmaf(sc, v.w, of));
         }
-        if (!ok) v = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""));
         *reinterpret_cast<float4 *>(newp + 4 + 4 * g) = v;
       }
     }
@@ -835,6 +840,9 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
         mw[8 + v * kMergeHead + kMergeBlk * beta + 4 * X + i] = SQ ? fmaf(acc[X][i], 256.f, z_tot) : acc[X][i];
   }
   __syncthreads();
+  if constexpr (NEW == step::kNewCodes) {
+    if (has_new && a.clear_xch && tid == (WAVES - 1) * 64) step::retire_new_token(a, b * a.num_kv_heads + kv);
+  }
 
   // ---- arrival (see the exchange below): counted now, while the waves merge
   const int bk = b * a.num_kv_heads + kv;

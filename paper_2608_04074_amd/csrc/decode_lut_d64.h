@@ -94,6 +94,13 @@ __device__ __forceinline__ void load_tv_rows(const DecodeArgs &a, const int kv, 
   }
 }
 
+// A call, as the rare path's registers cost this kernel up to 1 us of 17 when it is
+// inlined (the head_dim-128 kernel is faster with it inlined).
+template <bool KS, bool FP8, bool SQ, bool TBF>
+__device__ __attribute__((noinline)) step::TokenValues form_apart(const step::TokenInputs in, const int lane) {
+  return step::form_new_token<kD, KS, FP8, SQ, TBF>(in, lane);
+}
+
 // (BSTEP: the kernel's own instantiation, so that each kernel inlines a
 // split pass of its own and the plain kernels compile as without the step)
 // NEW == kNewCodes: a step whose token comes from encoder workgroups
@@ -448,7 +455,13 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
     // the last wave, which has the fewest rounds of a short split
     if (has_new && wave == WAVES - 1) {
       uint32_t code = 0, scale = 0, sq = 0;
-      const bool ok = step::take_new_token<kL, KS, SQ>(a, b * a.num_kv_heads + kv, lane, code, scale, sq);
+      const bool there = step::take_new_token<kL, KS, SQ>(a, b * a.num_kv_heads + kv, lane, code, scale, sq);
+      if (__builtin_expect_with_probability(!there, 0, 0.99999)) {
+        const step::TokenValues t = form_apart<KS, FP8, SQ, TBF>(step::token_inputs<kD, TBF>(a, b, kv), lane);
+        code = t.code;
+        scale = t.scale;
+        sq = t.sq;
+      }
       const int g = lane & (kL - 1);
       half8_t e = {0, 0, 0, 0, 0, 0, 0, 0};
       if (lane < kL) e = *reinterpret_cast<const half8_t *>(smem + code * 256 + g * 16);
@@ -465,7 +478,6 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
           const float sc = __uint_as_float(sq << 16), of = __uint_as_float(sq & 0xffff0000u);
           v = make_float4(fmaf(sc, v.x, of), fmaf(sc, v.y, of), fmaf(sc, v.z, of), fmaf(sc, v.w, of));
         }
-        if (!ok) v = make_float4(__builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""), __builtin_nanf(""));
         *reinterpret_cast<float4 *>(newp + kH + 4 * g) = v;
       }
     }
@@ -494,6 +506,9 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
   }
 
   __syncthreads();  // every wave is done with the table before it becomes merge scratch
+  if constexpr (NEW == step::kNewCodes) {
+    if (has_new && a.clear_xch && tid == (WAVES - 1) * 64) step::retire_new_token(a, b * a.num_kv_heads + kv);
+  }
   float *merge = reinterpret_cast<float *>(smem + kMergeBase);
   float *mw = merge + wave * kMergeFloats;  // [0..8) m, [8..16) l, [16 + h*64 + d) acc
   const int head = lane & 7;

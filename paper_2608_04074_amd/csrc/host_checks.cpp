@@ -49,6 +49,9 @@ uint32_t next_epoch(bool captured) {
   return e;
 }
 
+static thread_local int g_new_token_polls = -1;
+int new_token_polls() { return g_new_token_polls >= 0 ? g_new_token_polls : 512; }
+
 nova_kv_status check_params(const nova_kv_params *p, bool need_encode, bool need_decode) {
   if (!p) return fail(NOVA_KV_ERR_INVALID_ARG, "params is NULL");
   if (p->num_kv_heads <= 0) return fail(NOVA_KV_ERR_INVALID_ARG, "num_kv_heads must be > 0");
@@ -248,5 +251,7 @@ void nova_kv_set_debug(int32_t on, int32_t num_blocks) {
   g_debug_blocks.store(num_blocks, std::memory_order_relaxed);
   g_debug.store(on ? 1 : 0, std::memory_order_relaxed);
 }
+
+void nova_kv_test_new_token_polls(int32_t polls) { g_new_token_polls = polls; }
 
 }  // extern "C"

@@ -25,6 +25,12 @@ bool aligned(const void *p, size_t a);
 // Tag of the split exchange of the next decode call: nonzero, new for every
 // call; odd for a call launched directly, even for a call captured in a graph.
 uint32_t next_epoch(bool captured);
+// How often the workgroup that attends a step's new token looks for its words
+// before it forms them itself: about 150 us, where the slowest encode takes 20 us
+// from the launch's start.  nova_kv_test_new_token_polls (exported, not in the
+// header) sets it for this thread's calls, 0 for words that never come; a
+// negative number restores it.
+int new_token_polls();
 
 nova_kv_status check_params(const nova_kv_params *p, bool need_encode, bool need_decode);
 nova_kv_status check_layout(const nova_kv_layout *lay);

@@ -82,6 +82,7 @@ struct DecodeArgs {
   // seq_lens[b] - 1 takes that token from xnew.  n_enc = 0: the splits' encoder
   // teams do it.
   int n_enc, enc_per_unit;
+  int new_polls;  // times that split looks for the token's words before it forms them itself (0: they are not handed over)
   // Tagged exchange of the head_dim-128 table kernel (64-bit words, the tag
   // in the high half): split partials [B*Hkv][n_split][kXchSlotWords] and
   // the new token's per-block results [B*Hkv][8 items][32].

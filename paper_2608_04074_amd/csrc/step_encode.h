@@ -66,7 +66,8 @@ struct Scratch {
 
 // Words of a new token handed to the split that attends it (DecodeArgs::xnew):
 // key code of group g, value code of group g, key scale, scalar-arm word.
-constexpr int kWordK = 0, kWordV = 32, kWordScale = 64, kWordSq = 65;
+constexpr int kWordK = 0, kWordV = 32, kWordScale = 64, kWordSq = 65, kWords = 66;
+constexpr int kWordCount = 127;  // who has finished with them, in a captured call
 struct NoPublish {
   __device__ __forceinline__ void operator()(int, uint32_t) const {}
 };
@@ -209,14 +210,39 @@ __device__ __forceinline__ void store_band_rows(const DecodeArgs &a, const int b
 // with TEAMS teams.
 //  * Without a band they hand the token's values to the split that holds its
 //    position as tagged words (HAND), while that split is still in its setup
-//    or token loop.  They come first in the dispatch order, so they run
-//    whatever waits for them.
+//    or token loop.  They come first in the dispatch order, so within one
+//    launch each XCD starts them before its decoding workgroups.  That says
+//    nothing of launches on other streams, whose workgroups may hold the CUs
+//    that an encoder needs: the split therefore looks for the words only
+//    new_polls times, then forms them itself (form_new_token), and no workgroup
+//    ever waits for one that may not have started.
 //  * With the token in the band nothing waits for them, and they come last.
 //    (In a full launch they would follow the decode: 32 sequences of 8192
 //    tokens in the deployed format took 75 us so, 63 in two launches.)
 constexpr int kNewNone = 0, kNewCodes = 1, kNewBand = 2;  // what a decoding workgroup does about the token
 
 constexpr int kWide = 8192;  // LDS bytes of a team's whole-token sums
+
+// Replays of a captured call repeat its tag, so the words of a unit are emptied
+// by the last of those who use them: its encoder workgroups, once their stores
+// have completed, and its reader, once it has the words or has given up on
+// them.  (Emptied by a reader that gave up, a word that comes later would be
+// taken for the next replay's.)  The count travels with the tag, as whatever a
+// call of another shape left in its word must not be taken for one.
+__device__ __forceinline__ void retire_new_token(const DecodeArgs &a, const int unit) {  // one thread
+  uint64_t *xn = a.xnew + static_cast<size_t>(unit) * 8 * 32;
+  const uint32_t all = static_cast<uint32_t>(a.enc_per_unit) + 1;
+  uint64_t old = lut::get_word(xn + kWordCount);
+  uint32_t count;
+  uint64_t now;
+  do {  // a failed exchange means that another of the `all` has counted in
+    count = lut::word_ready(a.epoch, old) ? static_cast<uint32_t>(old) + 1 : 1;
+    now = count == all ? 0 : (static_cast<uint64_t>(a.epoch) << 32) | count;
+  } while (!__hip_atomic_compare_exchange_strong(xn + kWordCount, &old, now, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                 __HIP_MEMORY_SCOPE_AGENT));
+  if (count == all)
+    for (int w = 0; w < kWords; ++w) lut::clear_word(xn + w);
+}
 
 // An encoder workgroup's work (number wg < n_enc).
 template <int D, int TEAMS, bool KS, bool FP8, bool SQ, bool TBF, bool HAND, class RowOf>
@@ -236,26 +262,29 @@ __device__ __forceinline__ void encode_workgroup(const DecodeArgs &a, uint8_t *s
   int phase = 0;  // shared by every copy of the meeting
   auto meet = [&] { team_meet(ctr + team, ++phase); };
   auto publish = [&](const int w, const uint32_t v) {
-    if constexpr (HAND) lut::put_word(a.epoch, xn + w, __uint_as_float(v));
+    if (HAND && a.new_polls > 0) lut::put_word(a.epoch, xn + w, __uint_as_float(v));
   };
   encode_token<D, KS, SQ, TBF>(a, ls[team], b, kv, e * TEAMS + team, TEAMS * a.enc_per_unit, row_of(b, kv, S - 1),
                                tid & 255, FP8, meet, publish, wide + team * (kWide / 8));
+  if (HAND && a.clear_xch) {
+    __builtin_amdgcn_s_waitcnt(0);  // this thread's words have landed
+    __syncthreads();
+    if (tid == 0) retire_new_token(a, unit);
+  }
 }
 
 // The handed-over words of a unit's new token, read by one whole wave: lane l
 // gets words l (key codes in lanes 0 .., value codes in lanes 32 ..), and
-// every lane the scale and the scalar-arm word in their formats.  A captured
-// call empties them, as replays repeat its tag.  False if a word never came
-// (not expected).
-constexpr int kNewSpin = 1 << 20;
+// every lane the scale and the scalar-arm word in their formats.  False if
+// some are not there yet.
 template <int L, bool KS, bool SQ>
 __device__ __forceinline__ bool take_new_token(const DecodeArgs &a, const int unit, const int lane, uint32_t &code,
                                                uint32_t &scale, uint32_t &sq) {
-  uint64_t *xn = a.xnew + static_cast<size_t>(unit) * 8 * 32;
+  const uint64_t *xn = a.xnew + static_cast<size_t>(unit) * 8 * 32;
   const int w = (lane & 32) + (lane & (L - 1));
-  uint64_t c, ks = 0, vq = 0;
-  for (int n = 0;; ++n) {
-    c = lut::get_word(xn + w);
+  for (int n = 1;; ++n) {
+    const uint64_t c = lut::get_word(xn + w);
+    uint64_t ks = 0, vq = 0;
     bool ready = lut::word_ready(a.epoch, c);
     if constexpr (KS) {
       ks = lut::get_word(xn + kWordScale);
@@ -265,19 +294,135 @@ __device__ __forceinline__ bool take_new_token(const DecodeArgs &a, const int un
       vq = lut::get_word(xn + kWordSq);
       ready = ready && lut::word_ready(a.epoch, vq);
     }
-    if (__all(ready)) break;
-    if (n == kNewSpin) return false;
+    if (__all(ready)) {
+      code = static_cast<uint32_t>(c) & 0xffu;
+      scale = static_cast<uint32_t>(ks);
+      sq = static_cast<uint32_t>(vq);
+      return true;
+    }
+    if (n >= a.new_polls) return false;
     __builtin_amdgcn_s_sleep(2);
   }
-  code = static_cast<uint32_t>(c) & 0xffu;
-  scale = static_cast<uint32_t>(ks);
-  sq = static_cast<uint32_t>(vq);
-  if (a.clear_xch) {
-    lut::clear_word(xn + w);
-    if (KS && lane == 0) lut::clear_word(xn + kWordScale);
-    if (SQ && lane == 0) lut::clear_word(xn + kWordSq);
+}
+
+// The same values formed by the reading wave itself, where its encoder has not
+// delivered them: fp64 sums and distances as in encode_block.h, one group after
+// the other.  It stores nothing; the encoder workgroup does, before the launch
+// ends.
+__device__ __forceinline__ double lane_f64(const double x, const int l) {  // uniform l
+  const unsigned long long u = static_cast<unsigned long long>(__double_as_longlong(x));
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<int>(u), l);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<int>(u >> 32), l);
+  return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
+}
+struct TokenInputs {  // of one (sequence, KV head)
+  const void *x[2], *t[2], *cb[2];  // key and value: row, transform, codebook of the KV head
+  const float *kbar;
+  int bf16;
+};
+struct TokenValues {  // as take_new_token hands them out
+  uint32_t code, scale, sq;
+};
+template <int D, bool KS, bool FP8, bool SQ, bool TBF>
+__device__ __forceinline__ TokenValues form_new_token(const TokenInputs in, const int lane) {
+  constexpr int L = D / kGroupDim;
+  uint32_t code = 0, scale = 0, sq = 0;
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    const bool key = side == 0;
+    const void *src = key ? in.x[0] : in.x[1], *tm = key ? in.t[0] : in.t[1], *cb = key ? in.cb[0] : in.cb[1];
+    auto element = [&](const int d) {  // element lane + d, minus k_bar for keys
+      const double x = in.bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(src)[lane + d]))
+                               : static_cast<double>(static_cast<const float *>(src)[lane + d]);
+      return key ? x - static_cast<double>(in.kbar[lane + d]) : x;
+    };
+    // coefficients lane and, at head_dim 128, lane + 64 (else u1 = u0)
+    double u0 = 0.0, u1 = 0.0;
+    auto rows = [&](const double x, const int first) {
+#pragma unroll 4
+      for (int r = 0; r < 64; ++r) {
+        const double xr = lane_f64(x, r);
+        const size_t row = static_cast<size_t>(first + r) * D + lane;
+        u0 = fma(xr, static_cast<double>(t1_value(tm, row, TBF)), u0);
+        if constexpr (D == 128) u1 = fma(xr, static_cast<double>(t1_value(tm, row + 64, TBF)), u1);
+      }
+    };
+    rows(element(0), 0);
+    if constexpr (D == 128) rows(element(64), 64);
+    else u1 = u0;
+    if (!key && SQ) {
+      double mn = fmin(u0, u1), mx = fmax(u0, u1);
+      for (int o = 32; o > 0; o >>= 1) {
+        mn = fmin(mn, __shfl_xor(mn, o, 64));
+        mx = fmax(mx, __shfl_xor(mx, o, 64));
+      }
+      const uint16_t zb = encblk::bf16_of(mn), sb = encblk::bf16_of((mx - mn) / 3.0);
+      const double zero = bf16_bits_to_float(zb), sc = bf16_bits_to_float(sb);
+      sq = sb | (static_cast<uint32_t>(zb) << 16);
+      auto level = [&](const double u) {
+        return sc > 0.0 ? static_cast<uint32_t>(fmin(fmax(rint((u - zero) / sc), 0.0), 3.0)) : 0u;
+      };
+      const uint32_t q0 = level(u0), q1 = level(u1);
+      uint32_t byte = 0u;  // of group lane mod L
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int c = 4 * (lane & (L - 1)) + j;
+        const uint32_t l0 = __shfl(q0, c & 63, 64), l1 = __shfl(q1, c & 63, 64);
+        byte |= (c < 64 ? l0 : l1) << (2 * j);
+      }
+      if (lane >= 32) code = byte;
+      continue;
+    }
+    if (key && KS) {
+      double n2 = D == 128 ? u0 * u0 + u1 * u1 : u0 * u0;
+      for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o, 64);
+      const double rho = sqrt(n2) / sqrt(static_cast<double>(D));
+      scale = encblk::bf16_of(rho);
+      u0 = rho > 0.0 ? u0 / rho : 0.0;
+      u1 = rho > 0.0 ? u1 / rho : 0.0;
+    }
+    // nearest codeword of each group: lane l takes codewords 4 l .. 4 l + 3
+#pragma unroll 1
+    for (int g = 0; g < L; ++g) {
+      double v[4], best = INFINITY;
+      int arg = 4 * lane;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = lane_f64(g >= 16 ? u1 : u0, (4 * g + i) & 63);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+#pragma clang fp contract(off)
+        const uint2 w = codeword(cb, FP8, static_cast<size_t>(g) * kCodebookSize + 4 * lane + j);
+        const double e0 = v[0] - static_cast<double>(half_bits_to_float(static_cast<uint16_t>(w.x & 0xffff)));
+        const double e1 = v[1] - static_cast<double>(half_bits_to_float(static_cast<uint16_t>(w.x >> 16)));
+        const double e2 = v[2] - static_cast<double>(half_bits_to_float(static_cast<uint16_t>(w.y & 0xffff)));
+        const double e3 = v[3] - static_cast<double>(half_bits_to_float(static_cast<uint16_t>(w.y >> 16)));
+        const double dist = e0 * e0 + e1 * e1 + e2 * e2 + e3 * e3;
+        if (dist < best) {
+          best = dist;
+          arg = 4 * lane + j;
+        }
+      }
+      for (int o = 32; o > 0; o >>= 1) {
+        const double ob = __shfl_xor(best, o, 64);
+        const int oa = __shfl_xor(arg, o, 64);
+        if (ob < best || (ob == best && oa < arg)) {
+          best = ob;
+          arg = oa;
+        }
+      }
+      if ((lane & (L - 1)) == g && (lane >= 32) == !key) code = static_cast<uint32_t>(arg);
+    }
   }
-  return true;
+  return TokenValues{code, scale, sq};
+}
+template <int D, bool TBF>
+__device__ __forceinline__ TokenInputs token_inputs(const DecodeArgs &a, const int b, const int kv) {
+  const size_t row = (static_cast<size_t>(b) * a.num_kv_heads + kv) * D * (a.new_bf16 ? 2 : 4);
+  const size_t cw = static_cast<size_t>(kv) * (D / kGroupDim) * kCodebookSize;
+  return TokenInputs{{static_cast<const uint8_t *>(a.k_new) + row, static_cast<const uint8_t *>(a.v_new) + row},
+                     {transform_of(a.t_k, kv, D, TBF), transform_of(a.t_v, kv, D, TBF)},
+                     {codebook_from(a.cb_k, a.cb_fp8, cw), codebook_from(a.cb_v, a.cb_fp8, cw)},
+                     a.kbar + kv * D, a.new_bf16};
 }
 
 }  // namespace step

@@ -5,8 +5,9 @@ Whatever the plan takes, the step must write the bytes of nova_kv_encode at
 seq_lens - 1 and return nova_kv_decode_attn over the result.  Every format, both
 head sizes; an empty sequence, a first token, lengths at the edges of rounds and
 splits, a window; contiguous and paged caches; and replays of a captured call
-(the handed-over words carry the captured call's tag, so the reader empties
-them).
+(the handed-over words carry the captured call's tag, so the last to use them
+empties them).  A split that does not find its token's words soon forms them
+itself: the same has to hold where they never come, or after one look.
 
 Tolerance: the step attends its token with fp32 probabilities, the decode with
 fp16 ones (2^-11 of one token's share): 5e-4 of the row norm."""
@@ -65,8 +66,19 @@ CASES = [
 ]
 
 
+@pytest.fixture
+def polls(nk, request):
+    """How often a split looks for its token's words, for this thread's calls
+    (None: as the library sets it; 0: they never come)."""
+    hook = nk._native.lib().nova_kv_test_new_token_polls
+    hook(-1 if request.param is None else request.param)
+    yield request.param
+    hook(-1)
+
+
+@pytest.mark.parametrize("polls", [None, 0, 1], indirect=True)
 @pytest.mark.parametrize("D,gqa,H,lens,cap,bs,window,fmt", CASES)
-def test_step_is_append_then_decode(nk, D, gqa, H, lens, cap, bs, window, fmt):
+def test_step_is_append_then_decode(nk, polls, D, gqa, H, lens, cap, bs, window, fmt):
     ks, sq, fp8 = (f in fmt.split() for f in ("ks", "sq", "fp8"))
     wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=H, num_q_heads=H * gqa)
     arr = dict(synth.bench_params(wl))
@@ -90,7 +102,7 @@ def test_step_is_append_then_decode(nk, D, gqa, H, lens, cap, bs, window, fmt):
     sinks = dev(rng.standard_normal(H * gqa), torch.float32)
     out = torch.empty((B, H * gqa, D), dtype=torch.float32, device="cuda")
     ws = torch.zeros(nk.decode_workspace_bytes(P, B, H * gqa, cap), dtype=torch.uint8, device="cuda")
-    what = f"step D={D} gqa={gqa} H={H} B={B} cap={cap} block={bs} window={window} {fmt}"
+    what = f"step D={D} gqa={gqa} H={H} B={B} cap={cap} block={bs} window={window} {fmt} polls={polls}"
 
     def pools():
         return dict(k=dev(ck, torch.uint8), v=dev(cv, torch.uint8), ks=bits(hks) if ks else None, sq=bits(hsq) if sq else None)
@@ -143,3 +155,40 @@ def test_step_is_append_then_decode(nk, D, gqa, H, lens, cap, bs, window, fmt):
         assert torch.equal(one["k"], two["k"]) and torch.equal(one["v"], two["v"])
         step()
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("polls", [None, 0, 1], indirect=True)
+@pytest.mark.parametrize("D,lens,cap", [(128, [2000], 2048), (128, [500, 0, 3], 512), (64, [150, 0, 3], 192)])
+def test_replay_leaves_no_words(nk, polls, D, lens, cap):
+    """Replays of a captured step repeat its tag: each leaves the workspace all
+    zero, whether the split took the handed-over words or gave up on them (its
+    encoder's words then come later), so none is there for the next one.  (One
+    split at head_dim 64, whose split partials are plain words.)"""
+    H, gqa, B = 2, 4, len(lens)
+    wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=H, num_q_heads=H * gqa)
+    P = nk.NovaKVParams.from_arrays(dict(synth.bench_params(wl)))
+    rng = np.random.default_rng(cap)
+    ck, cv = (dev(rng.integers(0, 256, (B, H, cap, D // 4), dtype=np.uint8), torch.uint8) for _ in range(2))
+    kn, vn = (dev(rng.standard_normal((B, H, D)), torch.bfloat16) for _ in range(2))
+    q = dev(rng.standard_normal((B, H * gqa, D)), torch.bfloat16)
+    lens_d = dev(lens, torch.int32)
+    out = torch.empty((B, H * gqa, D), dtype=torch.float32, device="cuda")
+    ws = torch.zeros(nk.decode_workspace_bytes(P, B, H * gqa, cap), dtype=torch.uint8, device="cuda")
+
+    def step():
+        nk.append_decode_attn(P, nk.CacheLayout.contiguous(cap), kn, vn, q, ck, cv, lens_d, cap, out=out, workspace=ws)
+
+    print(f"[gpu-case] replays of a captured step D={D} lens={lens} polls={polls}", flush=True)
+    step()
+    torch.cuda.synchronize()
+    ref = out.clone()
+    ws.zero_()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        step()
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert not ws.any()
+        close(out, ref, f"replayed step D={D} lens={lens}")
