@@ -1352,7 +1352,7 @@ __device__ __forceinline__ void unit_pass(const DecodeArgs &a, uint8_t *smem, co
   const int t0 = lo + split * a.chunk;  // splits tile the span read from the pools
   // the split that holds the new token (the last position attended) reads the
   // pools up to it
-  const bool has_new = NEW == step::kNewCodes && S > 0 && split == (S - 1 - lo) / a.chunk;
+  const bool has_new = NEW == step::kNewCodes && position_in_pool(a.layout, S - 1) && split == (S - 1 - lo) / a.chunk;
   const int t1 = min(has_new ? S - 1 : tend, lo + (split + 1) * a.chunk);
   const size_t row0 = static_cast<size_t>(b) * a.num_q_heads + kv * G;
   // Fused step: the splits with pool tokens (at least split 0) share the encode

@@ -187,7 +187,7 @@ __device__ __forceinline__ void encode_token(const DecodeArgs &a, Scratch<D> &ls
 template <int D>
 __device__ __forceinline__ void store_band_rows(const DecodeArgs &a, const int b, const int kv, const int pos) {
   const int tid = threadIdx.x;
-  if (tid >= 2 * D) return;
+  if (tid >= 2 * D || !position_in_pool(a.layout, pos)) return;
   const int side = tid / D, d = tid % D;
   const void *src = side ? a.v_new : a.k_new;
   const size_t idx = (static_cast<size_t>(b) * a.num_kv_heads + kv) * D + d;
@@ -251,7 +251,7 @@ __device__ __forceinline__ void encode_workgroup(const DecodeArgs &a, uint8_t *s
   if (unit >= a.batch * a.num_kv_heads) return;  // n_enc is rounded up
   const int b = unit / a.num_kv_heads, kv = unit - b * a.num_kv_heads;
   const int S = a.seq_lens[b];
-  if (S <= 0) return;
+  if (!position_in_pool(a.layout, S - 1)) return;  // (an empty sequence; its reader tests the same)
   const int tid = threadIdx.x, team = tid >> 8;
   Scratch<D> *ls = reinterpret_cast<Scratch<D> *>(smem);
   double *wide = reinterpret_cast<double *>(smem + TEAMS * sizeof(Scratch<D>));

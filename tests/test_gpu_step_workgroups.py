@@ -192,3 +192,37 @@ def test_replay_leaves_no_words(nk, polls, D, lens, cap):
         torch.cuda.synchronize()
         assert not ws.any()
         close(out, ref, f"replayed step D={D} lens={lens}")
+
+
+@pytest.mark.parametrize("D,fmt,bs,band", [(64, "", None, False), (128, "ks sq", 16, False), (64, "ks", 32, False),
+                                           (128, "ks sq", 16, True)])
+def test_a_length_past_the_capacity_stores_nothing(nk, D, fmt, bs, band):
+    """seq_lens one past a sequence's capacity is a caller's mistake; the step
+    stores nothing of that token, as the append does (the rows after the
+    sequence's are another's, in bounds of the pools here)."""
+    ks, sq = (f in fmt.split() for f in ("ks", "sq"))
+    H, gqa, B, cap, L = 2, 4, 3, 192, D // 4
+    wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=H, num_q_heads=H * gqa)
+    arr = dict(synth.bench_params(wl))
+    if sq:
+        arr["cb_v"] = None
+    P = nk.NovaKVParams.from_arrays(arr, key_scale=ks, sq_values=sq)
+    bps = 1 if bs is None else cap // bs
+    lay = (nk.CacheLayout.contiguous(cap) if bs is None else
+           nk.CacheLayout(bs, bps, torch.arange(B * bps, dtype=torch.int32, device="cuda").reshape(B, bps)))
+    shape = (B * bps, H, cap if bs is None else bs)
+    rng = np.random.default_rng(D)
+    pools = [dev(rng.integers(0, 256, shape + (L,), dtype=np.uint8), torch.uint8) for _ in range(2)]
+    pools += [bits(ocodec.bf16_bits(np.ones(shape)))] if ks else [None]
+    pools += [bits(ocodec.bf16_bits(np.ones(shape + (2,))))] if sq else [None]
+    bnd = nk.Band(4, 16, *(torch.zeros((B, H, 20, D), dtype=torch.bfloat16, device="cuda") for _ in range(2))) if band else None
+    kept = pools + ([bnd.k, bnd.v] if band else [])
+    before = [None if x is None else x.clone() for x in kept]
+    kn, vn = (dev(rng.standard_normal((B, H, D)), torch.bfloat16) for _ in range(2))
+    q = dev(rng.standard_normal((B, H * gqa, D)), torch.bfloat16)
+    print(f"[gpu-case] step past the capacity D={D} {fmt} block={bs} band={band}", flush=True)
+    nk.append_decode_attn(P, lay, kn, vn, q, pools[0], pools[1], dev([cap + 1, 0, 0], torch.int32), cap,
+                          k_scales=pools[2], v_sq=pools[3], band=bnd)
+    torch.cuda.synchronize()
+    for x, y in zip(kept, before):
+        assert x is None or torch.equal(x, y)
