@@ -186,7 +186,8 @@ __global__ void __launch_bounds__(256) encode_small(EncodeArgs a) {
 //    2. the 8 scores of that block again in fp32, for the index and the
 //       runner-up;
 //    3. where the runner-up is nearer than the error bound of both (a few
-//       tokens of 10^4), the wave searches that token's group in fp64.
+//       tokens of 10^4), the wave searches that token's group in fp64; a group
+//       with many such tokens is scored again first (kMany).
 //    Group scale: codewords times a power of two, so that the largest
 //    coordinate is in [32, 64); the token by a power of two of its own.  The
 //    bound: an MFMA of this form errs by at most 2^-23.5 of the sum of its
@@ -204,6 +205,14 @@ __global__ void __launch_bounds__(256) encode_small(EncodeArgs a) {
 // wait at a time before); 2 x 6001 tokens of head_dim 64 in the deployed format:
 // 436 us (321 of them a workgroup per token for the scalar arm), 96, now 72 us.
 constexpr int kTileWaves = 8;
+// More undecided tokens of a group than this (of 64), and at the end it is scored
+// once more without its repeated codewords (fp8 rounding of a group of little
+// variance, empty clusters, zeros of either sign): scoring takes as long as three
+// of the searches in fp64 that it spares.  8 x 2048 tokens, 8 KV heads of 128,
+// every codeword twice: 3881 us token by token, 474 so (593 with all scores in
+// fp64); keys with a scale 3279 and 540.  Well-spread codebooks: 2.5% slower at
+// head_dim 128 for the registers that the end takes, the same at 64.
+constexpr int kMany = 16;
 constexpr int kSelPart = 8192;  // LDS bytes before the search's staging, for the per-token reductions
 
 template <int D, int NTT>
@@ -307,9 +316,12 @@ __device__ __forceinline__ int group_exponent(const uint32_t big) {
 }
 
 // Codewords 4 lane .. +3 of a group, as loaded (raw): scaled, with their norms,
-// into the wave's staging.  Returns the largest magnitude's fp16 bits.
+// into the wave's staging.  Returns the largest magnitude's fp16 bits.  The
+// codewords of `out` (bit j: 4 lane + j) get a norm that keeps them from being
+// the nearest or the runner-up of any token.
 template <bool FP8>
-__device__ __forceinline__ uint32_t stage_group(const uint2 (&raw)[4], uint8_t *stage, const int lane) {
+__device__ __forceinline__ uint32_t stage_group(const uint2 (&raw)[4], uint8_t *stage, const int lane,
+                                                const uint32_t out = 0u) {
   uint2 w[4];
   uint32_t big = 0u;
 #pragma unroll
@@ -332,6 +344,7 @@ __device__ __forceinline__ uint32_t stage_group(const uint2 (&raw)[4], uint8_t *
       const f16x2 cx = __builtin_bit_cast(f16x2, c.x), cy = __builtin_bit_cast(f16x2, c.y);
       const float c0 = cx[0], c1 = cx[1], c2 = cy[0], c3 = cy[1];
       float n = fmaf(c3, c3, fmaf(c2, c2, fmaf(c1, c1, c0 * c0)));
+      if (out >> j & 1u) n = 60000.f;  // a norm is at most 4 * 64^2, and f at least 2^-14
       asm volatile("" : "+v"(n));  // hi is f16 of the rounded n everywhere (no product fused into the conversion)
       const _Float16 hi = static_cast<_Float16>(n);
       const _Float16 lo = static_cast<_Float16>(n - static_cast<float>(hi));
@@ -343,28 +356,82 @@ __device__ __forceinline__ uint32_t stage_group(const uint2 (&raw)[4], uint8_t *
   return big;
 }
 
+// Bit j: codeword 4 lane + j of the group (fp16) repeats one of a smaller index
+// (zeros of either sign are the same), which is then never the answer.  Equal codewords meet in a hash table in the
+// wave's staging; three tables, so that hardly one is missed (a missed one costs
+// time: tokens near it are searched in fp64).
+template <bool FP8>
+__device__ __forceinline__ uint32_t repeated(const uint2 (&raw)[4], uint8_t *stage, const int lane) {
+  const f16x2 zero = {0, 0};
+  uint2 w[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    w[j] = codeword_f16(raw[j], FP8);  // x + 0 is +0 for x = -0
+    w[j] = make_uint2(__builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, w[j].x) + zero),
+                      __builtin_bit_cast(uint32_t, __builtin_bit_cast(f16x2, w[j].y) + zero));
+  }
+  uint2 *all = reinterpret_cast<uint2 *>(stage);
+  uint32_t *table = reinterpret_cast<uint32_t *>(stage + 2048);  // [512]: smallest index with this hash
+  uint32_t out = 0u;
+  asm volatile("" ::: "memory");  // the group before is read; a wave's LDS operations run in order
+#pragma unroll
+  for (int j = 0; j < 4; ++j) all[4 * lane + j] = w[j];
+#pragma unroll 1
+  for (int round = 0; round < 3; ++round) {
+    const uint32_t mul = round == 0 ? 0x9e3779b1u : (round == 1 ? 0x85ebca77u : 0xc2b2ae3du);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) table[64 * i + lane] = ~0u;
+    asm volatile("" ::: "memory");
+    uint32_t h[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      h[j] = ((w[j].x ^ (w[j].y * 0x27d4eb2fu)) * mul) >> 23;
+      if (!(out >> j & 1u))
+        __hip_atomic_fetch_min(table + h[j], static_cast<uint32_t>(4 * lane + j), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    }
+    asm volatile("" ::: "memory");
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint32_t first = min(table[h[j]], 255u);
+      const uint2 c = all[first];
+      if (first < static_cast<uint32_t>(4 * lane + j) && c.x == w[j].x && c.y == w[j].y) out |= 1u << j;
+    }
+    asm volatile("" ::: "memory");
+  }
+  return out;
+}
+
+// The group at codeword cw staged again, its repeated codewords left out.
+template <bool FP8>
+__device__ __forceinline__ uint32_t stage_unrepeated(const void *cb, const size_t cw, uint8_t *stage, const int lane) {
+  uint2 raw[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) raw[j] = codeword_raw(cb, FP8, cw + 4 * lane + j);
+  return stage_group<FP8>(raw, stage, lane, repeated<FP8>(raw, stage, lane));
+}
+
 // Stages 1 and 2 of the search of a staged group: the code of each token (one
 // per lane; NB 32-token tiles), and whether it has to be searched in fp64 (flag).
 // big: stage_group's result; stage, arow: the wave's staging and the lane's
-// operand rows in it; us: the token's coefficients, exact up to fp32 rounding,
+// operand rows in it; u: the token's coefficients, exact up to fp32 rounding,
 // or each within err of its value (APPROX).
 template <int NB, bool APPROX = false>
 __device__ __forceinline__ int score_group(const uint32_t big, const uint8_t *stage, const uint8_t *arow, const int lane,
-                                           float (&us)[4], const float err, bool &flag) {
+                                           const float (&u)[4], const float err, bool &flag) {
   const uint32_t half = lane >> 5;
   const int ec = group_exponent(big);
   // token operand: w = -2 u scaled to below 128, as hi and lo; f weighs the
   // norms, o makes the scores about squared distances
-  float ws[4], f, o, a2;
+  float us[4], ws[4], f, o, a2;
   int eu;
   {
-    const float um = fmaxf(fmaxf(fabsf(us[0]), fabsf(us[1])), fmaxf(fabsf(us[2]), fabsf(us[3])));
+    const float um = fmaxf(fmaxf(fabsf(u[0]), fabsf(u[1])), fmaxf(fabsf(u[2]), fabsf(u[3])));
     eu = max(um > 0.f ? __builtin_amdgcn_frexp_expf(um) - 1 : ec, ec);
     flag = eu - ec > 14 || big >= 0x7c00u;  // f below fp16's normal range, or a codeword that is not finite
     a2 = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      us[i] = ldexpf(us[i], 5 - eu);
+      us[i] = ldexpf(u[i], 5 - eu);
       a2 = fmaf(us[i], us[i], a2);
       ws[i] = -2.f * us[i];
     }
@@ -461,13 +528,15 @@ __device__ __forceinline__ int score_group(const uint32_t big, const uint8_t *st
     }
   }
   const float next = fminf(sb, v2), gap = next - v1;
-  float bound = 0x1p-16f * (2.f * a2 + fabsf(v1)) + 0x1p-14f;
+  // (the terms of a score add up to at most 2^16, however large the token)
+  float bound = 0x1p-16f * (fminf(2.f * a2, 65536.f) + fabsf(v1)) + 0x1p-14f;
   if constexpr (APPROX) {
     // two scores differ by 2 (c1 - c2) . u: an error of E in each coordinate
-    // moves their gap by at most 4 E (|u - c1| + |u - c2| + 4 E), the
-    // distances about the runner-up's where the gap is small
+    // moves their gap by at most 4 E |c1 - c2|, where |c1 - c2| <= |u - c1| +
+    // |u - c2| + 4 E, the distances about the runner-up's where the gap is
+    // small, and <= 2 * 128 of the scaled codewords
     const float es = err * __builtin_amdgcn_exp2f(0.5f * static_cast<float>(10 - ec - eu));
-    bound += 8.f * es * (__builtin_amdgcn_sqrtf(fmaxf(next + (a2 - o), 0.f)) + 2.f * es);
+    bound += 8.f * es * (__builtin_amdgcn_sqrtf(fminf(fmaxf(next + (a2 - o), 0.f), 16384.f * f)) + 2.f * es);
   }
   flag = flag || !(gap > bound);
   return static_cast<int>(8 * blk + (__float_as_uint(v1) & 7u));
@@ -478,11 +547,11 @@ __device__ __forceinline__ int score_group(const uint32_t big, const uint8_t *st
 // 16-byte loads where the inputs' address allows them, single elements
 // otherwise.
 template <int NK, class Index>
-__device__ __forceinline__ void load_inputs(const EncodeArgs &a, const void *src, uint4 (&x)[NK], Index index) {
-  if (a.in_bf16) {
+__device__ __forceinline__ void load_inputs(const int in_bf16, const int in_vec, const void *src, uint4 (&x)[NK], Index index) {
+  if (in_bf16) {
     const uint16_t *p = static_cast<const uint16_t *>(src);
     uint2 h[NK];
-    if (a.in_vec) {
+    if (in_vec) {
 #pragma unroll
       for (int k = 0; k < NK; ++k) h[k] = *reinterpret_cast<const uint2 *>(p + index(k));
     } else {
@@ -498,7 +567,7 @@ __device__ __forceinline__ void load_inputs(const EncodeArgs &a, const void *src
 #pragma unroll
     for (int k = 0; k < NK; ++k)
       x[k] = make_uint4(h[k].x << 16, h[k].x & 0xffff0000u, h[k].y << 16, h[k].y & 0xffff0000u);
-  } else if (a.in_vec) {
+  } else if (in_vec) {
 #pragma unroll
     for (int k = 0; k < NK; ++k) x[k] = *reinterpret_cast<const uint4 *>(static_cast<const uint32_t *>(src) + index(k));
   } else {
@@ -570,7 +639,7 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a, con
     const int d = 4 * (tid % C4), s0 = tid / C4;
     const float4 kb = side == 0 ? *reinterpret_cast<const float4 *>(a.kbar + kv * D + d) : make_float4(0.f, 0.f, 0.f, 0.f);
     uint4 x[NK];  // fp32 bits
-    load_inputs<NK>(a, src, x, [&](const int k) {  // past the last token the last one is read again
+    load_inputs<NK>(a.in_bf16, a.in_vec, src, x, [&](const int k) {  // past the last token the last one is read again
       return (static_cast<size_t>(min(n0 + s0 + k * TP, n_tok - 1)) * a.num_kv_heads + kv) * D + d;
     });
 #pragma unroll
@@ -749,11 +818,9 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a, con
   auto group_cw = [&](const int k) { return cw0 + static_cast<size_t>(g0 + k) * kCodebookSize; };
 #pragma unroll
   for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(0) + 4 * lane + j);
-  uint32_t code_acc = 0u;
-#pragma unroll
-  for (int k = 0; k < (SPLIT ? 1 : 4); ++k) {
-    // token side first: coordinate rows to lane = token
-    double u[4] = {0.0, 0.0, 0.0, 0.0};
+  // coefficients of the wave's group k, lane = token
+  auto coefficients = [&](const int k, double (&u)[4]) {
+    u[0] = u[1] = u[2] = u[3] = 0.0;
     if (quarter) {
       if (lane < 16 * NTT) {
         const double *ur = quad + tok * T_::RQ + 4 * ot;
@@ -761,33 +828,41 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a, con
         for (int i = 0; i < 4; ++i) u[i] = ur[i] + ur[TOK * T_::RQ + i];
       }
     } else {
+      const int c = SPLIT ? only : k;
 #pragma unroll
-      for (int j = 0; j < NTT; ++j) {
-        if constexpr (SPLIT)
-          u[j] = only == 0 ? acc[j][0] : (only == 1 ? acc[j][1] : (only == 2 ? acc[j][2] : acc[j][3]));
-        else
-          u[j] = acc[j][k];
-      }
+      for (int j = 0; j < NTT; ++j) u[j] = c == 0 ? acc[j][0] : (c == 1 ? acc[j][1] : (c == 2 ? acc[j][2] : acc[j][3]));
       transpose_rows(u);  // u[i]: coordinate i of token `lane`
     }
-
-    bool flag;
-    float us[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) us[i] = static_cast<float>(u[i]);
-    const uint2 cur[4] = {rn[0], rn[1], rn[2], rn[3]};
-    if (k + 1 < (SPLIT ? 1 : 4)) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
-    }
-    int code = score_group<NTT == 4 ? 2 : 1>(stage_group<FP8>(cur, stage, lane), stage, arow, lane, us, 0.f, flag);
-    flag = flag && lane < 16 * NTT;
-    for (unsigned long long todo = __ballot(flag); todo; todo &= todo - 1) {
+  };
+  // the undecided tokens (todo) of group k, in fp64
+  auto decide = [&](unsigned long long todo, const int k, const double (&u)[4], int &code) {
+    for (; todo; todo &= todo - 1) {
       const int l = __builtin_ctzll(todo);
       const double uu[4] = {readlane_f64(u[0], l), readlane_f64(u[1], l), readlane_f64(u[2], l), readlane_f64(u[3], l)};
       const int c = search_exact<FP8>(cb, group_cw(k), lane, uu);
       if (lane == l) code = c;
     }
+  };
+  uint32_t code_acc = 0u, again = 0u;  // again: bit k, group k has many undecided tokens
+#pragma unroll
+  for (int k = 0; k < (SPLIT ? 1 : 4); ++k) {
+    double u[4];
+    coefficients(k, u);
+    const uint2 cur[4] = {rn[0], rn[1], rn[2], rn[3]};
+    if (k + 1 < (SPLIT ? 1 : 4)) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
+    }
+    float us[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) us[i] = static_cast<float>(u[i]);
+    bool flag;
+    int code = score_group<NTT == 4 ? 2 : 1>(stage_group<FP8>(cur, stage, lane), stage, arow, lane, us, 0.f, flag);
+    const unsigned long long todo = __ballot(flag && lane < 16 * NTT);
+    if (__popcll(todo) > kMany)
+      again |= 1u << k;
+    else
+      decide(todo, k, u, code);
     code_acc = SPLIT ? static_cast<uint32_t>(code) : (code_acc >> 8) | (static_cast<uint32_t>(code) << 24);
   }
   if (stored) {
@@ -795,6 +870,19 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a, con
       pool[off + g0] = static_cast<uint8_t>(code_acc);
     else
       *reinterpret_cast<uint32_t *>(pool + off + g0) = code_acc;
+  }
+#pragma unroll 1
+  for (; again; again &= again - 1) {
+    const int k = __builtin_ctz(again);
+    double u[4];
+    float us[4];
+    coefficients(k, u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) us[i] = static_cast<float>(u[i]);
+    bool flag;
+    int code = score_group<NTT == 4 ? 2 : 1>(stage_unrepeated<FP8>(cb, group_cw(k), stage, lane), stage, arow, lane, us, 0.f, flag);
+    decide(__ballot(flag && lane < 16 * NTT), k, u, code);
+    if (stored) pool[off + g0 + k] = static_cast<uint8_t>(code);
   }
 }
 
@@ -859,7 +947,7 @@ __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, 
   constexpr uint32_t kLo = TOK * RH * 2, kPlanes = 2 * kLo;
   constexpr uint32_t kTok = kPlanes > T_::BYTES_SEARCH ? kPlanes : T_::BYTES_SEARCH;  // per token: exponent, norm
   constexpr int KS = D / 32;                        // contraction steps of 32
-  __shared__ __attribute__((aligned(16))) uint8_t smem[kTok + TOK * 8];
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kTok + TOK * 8 + NS * NT * 8];
   const int kv = blockIdx.y, side = first_side + blockIdx.z;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -888,8 +976,9 @@ __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, 
   const int tok = 16 * NTT * th + lane;
   float uf[NS][4][4];  // [s][k][i]: coordinate i of group 4 ot + k, token `tok` of tile s
   float err[NS];
-  size_t off[NS];
-  bool stored[NS];
+  // code rows of the lane's tokens (kNoRow: not stored), in LDS until the end
+  constexpr size_t kNoRow = ~static_cast<size_t>(0);
+  size_t *rows = reinterpret_cast<size_t *>(smem + kTok + TOK * 8) + wave * 64 * NS + lane;
 
   f16x8 thi[KS], tlo[KS];  // T split, with the wave's scale and its largest column norm
   float tnorm = 0.f;
@@ -898,11 +987,11 @@ __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, 
   for (int s = 0; s < NS; ++s) {
     const int n0 = first + s * TOK;
     uint4 x[NK];  // fp32 bits
-    load_inputs<NK>(a, src, x, [&](const int k) {
+    load_inputs<NK>(a.in_bf16, a.in_vec, src, x, [&](const int k) {
       return (static_cast<size_t>(min(n0 + s0 + k * TP, n_tok - 1)) * a.num_kv_heads + kv) * D + d4;
     });
-    stored[s] = n0 + tok < n_tok;
-    const int tok_b = stored[s] ? (n0 + tok) / a.n_new : 0, tok_t = n0 + tok - tok_b * a.n_new;
+    bool stored = n0 + tok < n_tok;
+    const int tok_b = stored ? (n0 + tok) / a.n_new : 0, tok_t = n0 + tok - tok_b * a.n_new;
     const int tok_p0 = a.start_pos[tok_b];
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
@@ -978,8 +1067,8 @@ __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, 
     }
     __syncthreads();
     const int tok_pos = tok_p0 + a.start_offset + tok_t;
-    stored[s] = stored[s] && position_in_pool(a.layout, tok_pos);
-    const int tok_blk = stored[s] ? tok_pos / a.layout.block_size : 0;
+    stored = stored && position_in_pool(a.layout, tok_pos);
+    const int tok_blk = stored ? tok_pos / a.layout.block_size : 0;
     int tok_phys = tok_b * a.layout.blocks_per_seq + tok_blk;
     if (a.layout.block_table) tok_phys = a.layout.block_table[tok_phys];
 
@@ -1016,8 +1105,9 @@ __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, 
       for (int k = 0; k < 4; ++k) uf[s][k][i] = ldexpf(uf[s][k][i], eu);
     }
     __syncthreads();  // every wave has read the inputs; the region is the next tile's or the search's
-    off[s] = ((static_cast<size_t>(tok_phys) * a.num_kv_heads + kv) * a.layout.block_size +
-                (tok_pos - tok_blk * a.layout.block_size)) * L;
+    rows[64 * s] = stored ? ((static_cast<size_t>(tok_phys) * a.num_kv_heads + kv) * a.layout.block_size +
+                             (tok_pos - tok_blk * a.layout.block_size)) * L
+                          : kNoRow;
   }
 
   uint8_t *stage = smem + kSelPart + wave * 4096;
@@ -1028,50 +1118,79 @@ __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, 
   auto group_cw = [&](const int k) { return cw0 + static_cast<size_t>(g0 + k) * kCodebookSize; };
 #pragma unroll
   for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(0) + 4 * lane + j);
-  uint32_t code_acc[NS] = {};
+  // the undecided tokens (todo) of group k, tile s, in fp64: a token's four
+  // coefficients, a lane adds D / 64 rows, then the search
+  auto decide = [&](unsigned long long todo, const int k, const int n0, int &code) {
+    for (; todo; todo &= todo - 1) {
+      const int l = __builtin_ctzll(todo);
+      const size_t idx = (static_cast<size_t>(n0 + 16 * NTT * th + l) * a.num_kv_heads + kv) * D;
+      double uu[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int i = 0; i < D / 64; ++i) {
+        const int row = lane + 64 * i;
+        double x = a.in_bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(src)[idx + row]))
+                             : static_cast<double>(static_cast<const float *>(src)[idx + row]);
+        if (side == 0) x -= static_cast<double>(a.kbar[kv * D + row]);
+        const float4 t = t4_value(load_t4(tm, static_cast<size_t>(row) * D + 4 * (g0 + k), TBF), TBF);
+        uu[0] = fma(x, static_cast<double>(t.x), uu[0]);
+        uu[1] = fma(x, static_cast<double>(t.y), uu[1]);
+        uu[2] = fma(x, static_cast<double>(t.z), uu[2]);
+        uu[3] = fma(x, static_cast<double>(t.w), uu[3]);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) uu[i] = wave_sum_f64(uu[i]);
+      const int c = search_exact<FP8>(cb, group_cw(k), lane, uu);
+      if (lane == l) code = c;
+    }
+  };
+  uint32_t code_acc[NS] = {}, again = 0u;  // again: bit 4 s + k, group k of tile s has many undecided tokens
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const uint2 cur[4] = {rn[0], rn[1], rn[2], rn[3]};
-    if (k < 3) {
-#pragma unroll
-      for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
-    }
     const uint32_t big = stage_group<FP8>(cur, stage, lane);
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
       const int n0 = first + s * TOK;
+      if (k < 3 && s == NS - 1) {  // the next group's codewords, in flight while the last tile is scored
+#pragma unroll
+        for (int j = 0; j < 4; ++j) rn[j] = codeword_raw(cb, FP8, group_cw(k + 1) + 4 * lane + j);
+      }
       bool flag;
       int code = score_group<2, true>(big, stage, arow, lane, uf[s][k], err[s], flag);
-      flag = flag && n0 + tok < n_tok;
-      for (unsigned long long todo = __ballot(flag); todo; todo &= todo - 1) {
-        // the token's four coefficients in fp64: a lane adds D / 64 rows
-        const int l = __builtin_ctzll(todo);
-        const size_t idx = (static_cast<size_t>(n0 + 16 * NTT * th + l) * a.num_kv_heads + kv) * D;
-        double uu[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-        for (int i = 0; i < D / 64; ++i) {
-          const int row = lane + 64 * i;
-          double x = a.in_bf16 ? static_cast<double>(bf16_bits_to_float(static_cast<const uint16_t *>(src)[idx + row]))
-                               : static_cast<double>(static_cast<const float *>(src)[idx + row]);
-          if (side == 0) x -= static_cast<double>(a.kbar[kv * D + row]);
-          const float4 t = t4_value(load_t4(tm, static_cast<size_t>(row) * D + 4 * (g0 + k), TBF), TBF);
-          uu[0] = fma(x, static_cast<double>(t.x), uu[0]);
-          uu[1] = fma(x, static_cast<double>(t.y), uu[1]);
-          uu[2] = fma(x, static_cast<double>(t.z), uu[2]);
-          uu[3] = fma(x, static_cast<double>(t.w), uu[3]);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) uu[i] = wave_sum_f64(uu[i]);
-        const int c = search_exact<FP8>(cb, group_cw(k), lane, uu);
-        if (lane == l) code = c;
-      }
+      const unsigned long long todo = __ballot(flag && n0 + tok < n_tok);
+      if (__popcll(todo) > kMany)
+        again |= 1u << (4 * s + k);
+      else
+        decide(todo, k, n0, code);
       code_acc[s] = (code_acc[s] >> 8) | (static_cast<uint32_t>(code) << 24);
       __builtin_amdgcn_sched_barrier(0);  // one tile's scores in registers at a time
     }
   }
 #pragma unroll
-  for (int s = 0; s < NS; ++s)
-    if (stored[s]) *reinterpret_cast<uint32_t *>(pool + off[s] + g0) = code_acc[s];
+  for (int s = 0; s < NS; ++s) {
+    const size_t row = rows[64 * s];
+    if (row != kNoRow) *reinterpret_cast<uint32_t *>(pool + row + g0) = code_acc[s];
+  }
+#pragma unroll 1
+  for (; again; again &= again - 1) {
+    const int e = __builtin_ctz(again), k = e & 3;
+    float u[4] = {0.f, 0.f, 0.f, 0.f}, er = err[0];
+#pragma unroll
+    for (int s = 0; s < NS; ++s) {
+      if (e >> 2 == s) er = err[s];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk)
+        if (e == 4 * s + kk)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) u[i] = uf[s][kk][i];
+    }
+    const int n0 = first + (e >> 2) * TOK;
+    bool flag;
+    int code = score_group<2, true>(stage_unrepeated<FP8>(cb, group_cw(k), stage, lane), stage, arow, lane, u, er, flag);
+    decide(__ballot(flag && n0 + tok < n_tok), k, n0, code);
+    const size_t row = rows[64 * (e >> 2)];
+    if (row != kNoRow) pool[row + g0 + k] = static_cast<uint8_t>(code);
+  }
 }
 
 // Two tiles per workgroup of encode_fast (its T split and its staged codewords

@@ -6,7 +6,10 @@ its codes are the fp64 argmin, the smallest index among equal distances.  Cases:
 tiles that straddle sequences, a tile of a few tokens, both launch shapes (one
 group per wave, and all four), both head sizes; codebooks far larger and far
 smaller than the coefficients (the group's and the token's scales), a repeated
-codeword (a tie), and a codeword that is not finite."""
+codeword (a tie), and a codeword that is not finite; and what leaves many tokens
+of a group undecided, which the group is then scored once more for: codebooks of
+mostly repeated codewords (zeros of both signs among them), groups of little
+variance, tokens far larger than the codebook."""
 
 import numpy as np
 import pytest
@@ -35,7 +38,7 @@ def dev(x, dtype):
 
 @pytest.mark.parametrize("D,B,n_new,H", [(128, 3, 5, 2), (128, 7, 13, 2), (64, 5, 33, 2), (64, 2, 129, 1),
                                          (128, 2, 1055, 4), (64, 3, 1400, 4)])
-@pytest.mark.parametrize("kind", ["plain", "ties", "scales"])
+@pytest.mark.parametrize("kind", ["plain", "ties", "scales", "repeated", "little variance", "large tokens"])
 def test_codes(nk, D, B, n_new, H, kind):
     wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=H, num_q_heads=H)
     params = dict(synth.bench_params(wl))
@@ -47,6 +50,11 @@ def test_codes(nk, D, B, n_new, H, kind):
             L = c.shape[1]
             c *= (2.0 ** np.array([12, -12, 3, -3, 0, 6, -20])[np.arange(L) % 7])[None, :, None, None].astype(np.float32)
             c[:, L - 1, 9, 2] = np.inf
+        elif kind == "repeated":
+            c[:, :, 40:] = c[:, :, 39 - np.arange(40, 256) % 37]
+            c[:, 1::4] *= 0.0  # zeros of both signs only
+        elif kind == "little variance":
+            c[:, ::2] *= 2.0 ** -10
         params[k] = c.astype(np.float16)
     P = nk.NovaKVParams.from_arrays(params)
     rng = np.random.default_rng(n_new)
@@ -56,6 +64,15 @@ def test_codes(nk, D, B, n_new, H, kind):
     if kind == "scales":  # tokens much larger and smaller than their neighbours
         s = torch.as_tensor(2.0 ** rng.integers(-6, 7, (B, n_new, 1, 1)))
         kk, vv = (kk.double() * s).to(torch.bfloat16), (vv.double() * s).to(torch.bfloat16)
+    elif kind == "large tokens":
+        kk, vv = (x * 512 for x in (kk, vv))
+    elif kind == "little variance":  # as little in the same groups' coefficients
+        w = torch.ones(D // 4, 4, dtype=torch.float64)
+        w[::2] = 2.0 ** -10
+        t = [torch.as_tensor(np.asarray(params[n], np.float64)) for n in ("t_k_inv_t", "t_v", "kbar")]
+        kk, vv = (torch.matmul((x.double() * w.reshape(-1))[..., None, :], m.transpose(1, 2).contiguous())[..., 0, :]
+                  for x, m in ((kk, t[0]), (vv, t[1])))
+        kk, vv = (kk + t[2]).float(), vv.float()
     pk = torch.zeros((B, H, cap, D // 4), dtype=torch.uint8, device="cuda")
     pv = torch.zeros_like(pk)
     print(f"[gpu-case] encode_tile D={D} B={B} n_new={n_new} H={H} {kind}", flush=True)
@@ -71,6 +88,8 @@ def test_codes(nk, D, B, n_new, H, kind):
                 got_k, got_v = hk[b, kv, s0:s0 + n_new], hv[b, kv, s0:s0 + n_new]
                 compare_codes(got_k, ck, gk, f"encode_tile D={D} {kind} b{b} kv{kv} K")
                 compare_codes(got_v, cv, gv, f"encode_tile D={D} {kind} b{b} kv{kv} V")
+                if kind == "repeated":  # never one that repeats another
+                    assert not (got_k[:, 0::4] >= 40).any() and not got_k[:, 1::4].any() and not got_v[:, 1::4].any()
                 if kind == "ties":
                     assert not (got_k == 100).any() and not (got_v == 100).any()
 
