@@ -177,12 +177,22 @@ DecodePlan plan_decode(int batch, int num_q_heads, int num_kv_heads, int head_di
     if (ng > max_group) max_group = ng;
   }
   p.off_cnt = 0;
-  // the gap after the counters held the pre-transformed queries and sink
-  // logits of a separate launch; a workspace keeps its size and layout
+  // The counters must be zero between calls, also where one workspace serves
+  // calls of several shapes: no call may store anything else where another's
+  // counters lie.  Plans with several splits have at most 384 units, so those of
+  // the kernels with plain partials end before kCounterBytes (3072 in the
+  // head_dim-128 table kernel, whose partials are far from there).  The partials
+  // start past them as far as the two gaps allow, which held the queries of a
+  // separate launch and a step's results, and keep a workspace's size and the
+  // exchange's place what they were.
+  constexpr size_t kCounterBytes = 3072;
   const size_t gap = align(align(static_cast<size_t>(units) * (1 + max_group) * sizeof(int)) + rows * head_dim * sizeof(float));
-  p.off_ml = align(gap + rows * sizeof(float));
-  p.off_acc = align(p.off_ml + rows * max_split * 2 * sizeof(float));
-  const size_t gap2 = align(p.off_acc + rows * max_split * head_dim * sizeof(float));  // likewise
+  const size_t gap2_bytes = static_cast<size_t>(units) * 8 * 32 * sizeof(float);
+  const size_t ml0 = align(gap + rows * sizeof(float));
+  p.off_ml = std::max(ml0, std::min(kCounterBytes, ml0 + gap2_bytes));
+  const size_t after_ml = align(rows * max_split * 2 * sizeof(float));
+  p.off_acc = p.off_ml + after_ml;
+  const size_t gap2 = align(ml0 + after_ml + rows * max_split * head_dim * sizeof(float));
   p.off_xch = align(gap2 + static_cast<size_t>(batch) * num_kv_heads * 8 * 32 * sizeof(float));
   p.off_xnew = align(p.off_xch + units * max_split * kXchSlotWords * sizeof(uint64_t));
   p.off_xgrp = align(p.off_xnew + static_cast<size_t>(units) * 8 * 32 * sizeof(uint64_t));

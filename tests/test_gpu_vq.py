@@ -149,3 +149,25 @@ def test_combine_of_many_splits(nk, n):
     ref = np.stack([oatt.decode_rows(q[b].astype(np.float64), codes[0, b, :m], codes[1, b, :m], hp, 1 / np.sqrt(D), 0, None)
                     for b, m in enumerate(lens)])
     assert_outputs_close(out.reshape(-1, D), ref.reshape(-1, D), tol=TOL32, what=f"decode_vq of {n} tokens")
+
+
+@pytest.mark.parametrize("D,cap", [(64, 20011), (64, 20016), (128, 20011)])
+def test_one_workspace_for_several_shapes(nk, D, cap):
+    """A workspace zero-filled once serves calls of any batch: the partials that
+    one sequence's splits leave lie past the arrival counters of 300."""
+    L, B = D // 4, 300
+    wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=1, num_q_heads=1)
+    P = nk.NovaKVParams.from_arrays(dict(synth.bench_params(wl)))
+    lay = nk.CacheLayout.contiguous(cap)
+    gen = torch.Generator(device="cuda").manual_seed(D)
+    ck, cv = (torch.randint(0, 256, (B, 1, cap, L), generator=gen, device="cuda", dtype=torch.uint8) for _ in range(2))
+    q = torch.randn((B, 1, D), generator=gen, device="cuda")
+    lens = torch.full((B,), cap, dtype=torch.int32, device="cuda")
+    print(f"[gpu-case] one workspace for batches of 1 and {B}, D={D} cap={cap}", flush=True)
+    ref = nk.decode_attn(P, lay, q, ck, cv, lens, cap)
+    ws = torch.zeros(max(nk.decode_workspace_bytes(P, b, 1, cap) for b in (1, B)), dtype=torch.uint8, device="cuda")
+    for n in (1, B, 1, B):
+        out = torch.full((n, 1, D), float("nan"), device="cuda")
+        nk.decode_attn(P, lay, q[:n].contiguous(), ck[:n], cv[:n], lens[:n].contiguous(), cap, out=out, workspace=ws)
+        assert_outputs_close(out.cpu().numpy().reshape(-1, D), ref[:n].cpu().numpy().reshape(-1, D).astype(np.float64),
+                             tol=TOL32 if cap % 16 else 2e-3, what=f"shared workspace D={D} cap={cap} batch {n}")
