@@ -145,3 +145,42 @@ def test_two_tiles_per_workgroup(nk, D, B, n_new, fmt):
         if not ks:
             compare_codes(whole[0][B - 1, kv, rows].cpu().numpy(), ck, gk, f"encode_fast pairs D={D} kv{kv} K")
         compare_codes(whole[1][B - 1, kv, rows].cpu().numpy(), cv, gv, f"encode_fast pairs D={D} kv{kv} V")
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("D,B,n_new,H,ks,sq", [(128, 3, 13, 2, False, False), (64, 3, 40, 2, True, True),
+                                               (128, 2, 1055, 4, False, False), (64, 3, 1400, 4, True, False),
+                                               (128, 3, 2735, 8, False, False), (64, 3, 5465, 8, False, True)])
+def test_inputs_at_any_address(nk, dtype, D, B, n_new, H, ks, sq):
+    """Keys and values that start one element into a buffer are loaded element by
+    element; the codes, scales and band rows are those of the same inputs at an
+    aligned address (which vectors load)."""
+    wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=H, num_q_heads=H)
+    arr = dict(synth.bench_params(wl))
+    if sq:
+        arr["cb_v"] = None
+    P = nk.NovaKVParams.from_arrays(arr, key_scale=ks, sq_values=sq)
+    gen = torch.Generator(device="cuda").manual_seed(n_new)
+    k, v = (torch.randn((B, n_new, H, D), generator=gen, device="cuda").to(dtype) for _ in range(2))
+    start = torch.zeros(B, dtype=torch.int32, device="cuda")
+
+    def shifted(x):
+        y = torch.empty(x.numel() + 1, dtype=x.dtype, device="cuda")[1:].view(x.shape)
+        y.copy_(x)
+        assert y.data_ptr() % 8 != 0
+        return y
+
+    def encode(kk, vv):
+        shape = (B, H, n_new)
+        out = {"k": torch.zeros(shape + (D // 4,), dtype=torch.uint8, device="cuda"),
+               "v": torch.zeros(shape + (D // 4,), dtype=torch.uint8, device="cuda"),
+               "ks": torch.zeros(shape, dtype=torch.bfloat16, device="cuda") if ks else None,
+               "sq": torch.zeros(shape + (2,), dtype=torch.bfloat16, device="cuda") if sq else None}
+        band = nk.Band(3, 20, *(torch.zeros((B, H, 23, D), dtype=torch.bfloat16, device="cuda") for _ in range(2)))
+        nk.encode(P, nk.CacheLayout.contiguous(n_new), kk, vv, start, out["k"], out["v"], k_scales=out["ks"],
+                  v_sq=out["sq"], band=band)
+        return [*(x for x in out.values() if x is not None), band.k, band.v]
+
+    print(f"[gpu-case] encode from an odd address D={D} B={B} n_new={n_new} {dtype} ks={ks} sq={sq}", flush=True)
+    for x, y in zip(encode(k, v), encode(shifted(k), shifted(v))):
+        assert torch.equal(x, y)
