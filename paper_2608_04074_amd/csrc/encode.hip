@@ -50,25 +50,6 @@ __device__ __forceinline__ uint16_t input_bf16_bits(const EncodeArgs &a, const v
   return static_cast<uint16_t>((f + 0x7fffu + ((f >> 16) & 1u)) >> 16);
 }
 
-// Coordinate q of codeword idx (an index over [Hkv][L][256]): its address,
-// the coordinate as loaded from there (the fp16 bits, or the fp8 byte,
-// zero-extended), and its value.  Codeword idx + j lies j * 4 elements on.
-__device__ __forceinline__ const uint8_t *coordinate_ptr(const void *cb, const bool fp8, const size_t idx, const int q) {
-  return static_cast<const uint8_t *>(cb) + (4 * idx + q) * (fp8 ? 1 : 2);
-}
-__device__ __forceinline__ uint32_t coordinate_raw(const uint8_t *p, const bool fp8, const int j) {
-  if (fp8) return p[4 * j];
-  return reinterpret_cast<const uint16_t *>(p)[4 * j];
-}
-__device__ __forceinline__ double coordinate_value(const uint32_t raw, const bool fp8) {
-  if (fp8) {
-    typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
-    const f16x2_t h = __builtin_amdgcn_cvt_scalef32_pk_f16_fp8(raw, 1.0f, false);
-    return static_cast<double>(static_cast<float>(h[0]));
-  }
-  return static_cast<double>(half_bits_to_float(static_cast<uint16_t>(raw)));
-}
-
 // Cross-lane steps on doubles without LDS traffic (each 32-bit half moves on
 // its own).  row_dpp: DPP within 16-lane rows (quad_perm xor 1 = 0xB1, xor 2 =
 // 0x4E, row_half_mirror = 0x141, row_mirror = 0x140).  swap_rows: the
@@ -103,21 +84,6 @@ __device__ __forceinline__ void swap_rows(double &x, double &y) {
   x = __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(h0) << 32) | l0));
   y = __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(h1) << 32) | l1));
 }
-// The largest x of the wave, in every lane (swapping x with a copy of itself
-// leaves x and the value of lane l ^ R in the two results).
-__device__ __forceinline__ double wave_max(double x) {
-  x = fmax(x, row_dpp<0xB1>(x));
-  x = fmax(x, row_dpp<0x4E>(x));
-  x = fmax(x, row_dpp<0x141>(x));
-  x = fmax(x, row_dpp<0x140>(x));
-  double y = x;
-  swap_rows<16>(x, y);
-  x = fmax(x, y);
-  y = x;
-  swap_rows<32>(x, y);
-  return fmax(x, y);
-}
-
 // Few new tokens (a decode step of a few sequences), plain formats: one workgroup
 // per (token, sequence, KV head, side, block of 8 groups).  A block needs 32 transform
 // columns (D x 32 fp32) and its 8 codebooks (16 KB), so each workgroup
@@ -886,7 +852,8 @@ __global__ void __launch_bounds__(64 * kTileWaves) encode_tile(EncodeArgs a, con
   }
 }
 
-// v[t] of lane row q becomes v[q] of lane row t (32-bit words).
+// The odd lane rows of x against the even ones of y, the high half of x against
+// the low one of y.
 __device__ __forceinline__ void swap16_f32(float &x, float &y) {
   const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
   const uint32_t a = s[0], b = s[1];
