@@ -731,18 +731,21 @@ __device__ __forceinline__ void split_pass(const DecodeArgs &a, uint8_t *smem, c
 
   // Up to two rounds per wave the rounds are assigned, so that the result does
   // not depend on which wave is free first (its reference rounds the fp16
-  // probabilities); a wave saves nothing by claiming there.  In a path of its
-  // own, without the claim: 131072 tokens of one sequence take 27.2 us instead of
-  // 27.5, and as a test in each claim of the loop it cost 64 x 32K tokens 0.5% of
-  // 249 us.  The step with encoder workgroups keeps the test, as the second path
-  // costs it registers (scalar arm, 2 x 3000 tokens: 17.1 us against 15.6).
-  constexpr bool own_path = NEW == step::kNewNone;
+  // probabilities); a wave saves nothing by claiming there.  In the plain and fp8
+  // formats in a path of its own, without the claim: 131072 tokens of one sequence
+  // take 27.2 us instead of 27.5, and as a test in each claim of the loop it cost
+  // 64 x 32K tokens 0.5% of 249 us.  The scaled formats would spill for a second
+  // path and take the claim's answer or not; the step with encoder workgroups
+  // keeps the test (a second path cost its scalar arm 17.1 us against 15.6, 2 x
+  // 3000 tokens).
+  constexpr bool own_path = NEW == step::kNewNone && !KS && !SQ;
   const bool assigned = nrounds <= 2 * WAVES;
   auto claim = [&](const int cur) -> int {
-    if (!own_path && assigned) return cur + WAVES;
+    if (NEW != step::kNewNone && assigned) return cur + WAVES;
     int v = 0;
     if (lane == 0) v = __hip_atomic_fetch_add(rctr, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    return __builtin_amdgcn_readfirstlane(v);
+    v = __builtin_amdgcn_readfirstlane(v);
+    return !own_path && assigned ? cur + WAVES : v;
   };
   if (own_path && assigned) {
     const int nxt = wave + WAVES;
