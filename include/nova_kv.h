@@ -207,7 +207,8 @@ typedef struct {
  * c minimising sum_i (u_i - cb[l][c][i])^2, u the group's coefficients; the
  * transform and the distances are evaluated in fp64.  In the key-scale format
  * the key side quantizes u / rho with rho = sqrt(sum of the D squared
- * coefficients, added in coordinate order) / sqrt(D) (u = 0 when rho = 0), and
+ * coefficients) / sqrt(D) (u = 0 when rho = 0; the sum in fp64, in an order that
+ * the call's shape decides, as the transform's is), and
  * stores rho rounded to fp32 and then to bf16 (each to nearest even).
  * batch == 0 or n_new == 0 is a valid no-op.
  */
@@ -219,7 +220,8 @@ nova_kv_status nova_kv_encode(const nova_kv_params *p, const nova_kv_layout *lay
 
 /*
  * Bytes of device workspace nova_kv_decode_attn needs for this shape (split
- * arrival counters, split partials, pre-transformed queries).  Returns 0 on
+ * arrival counters, split partials and exchange words).  One workspace may serve
+ * calls of several shapes, as large as the largest needs.  Returns 0 on
  * invalid input.
  */
 size_t nova_kv_decode_workspace_bytes(const nova_kv_params *p, int32_t batch,
@@ -299,16 +301,20 @@ nova_kv_status nova_kv_decode_attn(const nova_kv_params *p, const nova_kv_layout
  *   all other arguments as in nova_kv_decode_attn (params also need t_k).
  *
  * out equals the output of nova_kv_decode_attn over the pools after that
- * append, up to fp32 rounding.  On 16-aligned blocks the step is a single
- * kernel launch where the plan finds that cheapest, and it then stores what
- * nova_kv_encode would:
+ * append, up to rounding: on the table kernels the decode rounds every token's
+ * probability to fp16, and a step that adds its token's term by itself does not
+ * round that one (2^-11 of the token's share).  On 16-aligned blocks the step is
+ * a single kernel launch where the plan finds that cheapest, and it then stores
+ * what nova_kv_encode would:
  *   - any format (key scale, scalar value arm, fp8) with a band whose n_rec
- *     >= 1: the workgroups that read the pools also encode the new token; it
- *     is the band's last row, stored in the launch and attended exactly from
- *     it, as the decode after the encode would;
+ *     >= 1: the new token is also encoded in the launch, by workgroups of their
+ *     own when it leaves CUs idle, else by those that read the pools; it is the
+ *     band's last row, stored in the launch and attended exactly from it, as the
+ *     decode after the encode would;
  *   - any format without a band, when the launch leaves CUs idle: workgroups of
  *     their own encode the new token and hand its codes to the split that
- *     holds its position, which attends it from them;
+ *     holds its position, which attends it from them (or forms them itself, if
+ *     work on other streams keeps those workgroups from starting);
  *   - head_dim 128, plain or fp8 codebooks, no band, over several splits per
  *     (sequence, KV head): the workgroups that read the pools encode between
  *     them, and the token's term is added after the split combine.

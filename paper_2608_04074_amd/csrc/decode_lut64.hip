@@ -35,8 +35,8 @@ void launch_d64(const DecodeArgs &a, const dim3 grid, const dim3 block, hipStrea
 
 hipError_t launch_decode_lut64(const DecodeArgs &a, hipStream_t stream) {
   // 16 waves, 4 per SIMD: the kernel fits in 128 VGPRs.  A step (append) runs
-  // here only with a band whose recent part holds the new token.
-  // (its encoder then in the first split to arrive), or with encoder workgroups.
+  // here only with a band whose recent part holds the new token (its encoder then
+  // in the first split to arrive), or with encoder workgroups.
   if (a.n_enc > 0 ? (!a.append || a.n_enc % 8 != 0 || (a.band_k && a.n_rec < 1))
                   : (a.append && !(a.band_k && a.n_rec >= 1)))
     return hipErrorInvalidValue;

@@ -26,9 +26,10 @@
 //    probabilities of just these tokens, hi in columns 0..7, lo in 8..15.
 //
 // What bounds it: LDS.  Per token and KV head 64 (D = 128) 8-byte gathers at
-// random codes, about 12 cycles of a CU with their bank conflicts (3.5 lanes
-// on the fullest bank pair for K, 2.4 for V), against 8 MFMA cycles and about
-// 20 VALU cycles per SIMD, i.e. 7 per CU.  A step of 16 sequences of up to 12000
+// random codes: 4 cycles of a CU, and 5.2 of bank conflicts (counted), of the
+// 9.6 that a token takes (4.0 ns).  Beside them 8 MFMA cycles and about 20 VALU
+// cycles per SIMD, i.e. 7 per CU.  The scalar arm at head_dim 128 spills 25 to 31
+// registers, some of them in the token loop.  A step of 16 sequences of up to 12000
 // tokens, 64 query and 8 KV heads of 128, 32-token pages: 51.8 us with the
 // encode of its token (74 MB of codes); three launches that gathered and
 // multiplied one coordinate at a time on the VALU took 2798 us.  Its error

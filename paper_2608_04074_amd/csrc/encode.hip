@@ -903,9 +903,10 @@ __device__ __forceinline__ float dpp_f32(const float x) {
 // token and group and lane in single tiles) and the staging of a group's
 // codewords (55) serve all of them.  One tile's coefficients are formed after
 // the other's in the same LDS, and scored one after the other, so that two
-// workgroups still share a CU (128 VGPRs, 42 KiB of LDS).  32 x 4096 tokens, 8 KV
-// heads of 128: 2111 us with the fp64 transform, 1508 with single tiles, 1445 in
-// pairs.
+// workgroups still share a CU (128 VGPRs, 50 KiB of LDS; pairs spill 39 registers,
+// single tiles 6).  32 x 4096 tokens, 8 KV heads of 128: 2111 us with the fp64
+// transform; single tiles and pairs side by side 1509 and 1476, with the groups
+// that are scored again (kMany) 2.5% more.
 template <int D, bool FP8, bool TBF, int NS>
 __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, const int first_side) {
   using T_ = TileShape<D, 4>;
@@ -1163,8 +1164,8 @@ __global__ void __launch_bounds__(64 * kTileWaves, 4) encode_fast(EncodeArgs a, 
 // Two tiles per workgroup of encode_fast (its T split and its staged codewords
 // serve both) once that leaves two launch rounds of two workgroups per CU; below
 // that one tile, which ends sooner: 2 x 1024 tokens, 8 KV heads of 128, 34.6 us in
-// single tiles; 2 x 4096 tokens 116.4 us in single tiles and 112.7 in pairs, 32 x
-// 4096 1508 and 1445, 4 x 12000 of head_dim 64 275 and 252.
+// single tiles.  Larger ones, single tiles and pairs: 2 x 4096 tokens 116.4 and
+// 112.7, 32 x 4096 1509 and 1476, 4 x 12000 of head_dim 64 275 and 252.
 constexpr int kPairWorkgroups = 1024;
 
 // TBF: the transforms are stored as bf16 (a compile-time choice, so that the

@@ -1,7 +1,7 @@
 """The allocation-free step (nova_kv_append_decode_attn_noalloc) against the
 step with a caller's workspace, on two calls in a row, the second with a
 smaller input: the stored codes bit-exact, the outputs within the parity
-tolerance (splits of more than twelve rounds hand their later rounds to
+tolerance (splits of more than 24 rounds hand their later rounds to
 whichever wave is free, so two runs of the same step agree up to rounding)."""
 
 import numpy as np
