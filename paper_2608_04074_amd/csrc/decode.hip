@@ -30,7 +30,7 @@ int workspace_splits(int batch, int num_kv_heads, int max_seq_len) {
 //
 // A step adds its token's encode, the cheapest of:
 //   workgroups  where units * (splits + 1..) fit the CUs (step_encode.h): next to
-//               nothing (a step of 2000 tokens, 8 KV heads: 14.9 us, against 19.6
+//               nothing (a step of 2000 tokens, 8 KV heads: 15.2 us, against 19.6
 //               by teams and 18.4 in two launches; in the deployed format
 //               with a band 22.9 against 31.0);
 //   teams       the splits encode between them, beside their token loops: about

@@ -226,3 +226,44 @@ def test_a_length_past_the_capacity_stores_nothing(nk, D, fmt, bs, band):
     torch.cuda.synchronize()
     for x, y in zip(kept, before):
         assert x is None or torch.equal(x, y)
+
+
+@pytest.mark.parametrize("D,fmt", [(128, ""), (64, "ks")])
+def test_steps_on_several_streams(nk, D, fmt):
+    """Four steps in flight at once, each on a stream and a workspace of its own,
+    whose encoder and decoding workgroups together are more than the CUs."""
+    H, gqa, B, cap, n = 8, 4, 15, 512, 4
+    ks = fmt == "ks"
+    wl = synth.get_workload("qwen3_8b" if D == 128 else "gptoss_pair").scaled(num_kv_heads=H, num_q_heads=H * gqa)
+    P = nk.NovaKVParams.from_arrays(dict(synth.bench_params(wl)), key_scale=ks)
+    lay, gen = nk.CacheLayout.contiguous(cap), torch.Generator(device="cuda").manual_seed(D)
+    rnd = lambda *s: torch.randn(s, generator=gen, device="cuda").to(torch.bfloat16)  # noqa: E731
+    lens = torch.full((B,), 500, dtype=torch.int32, device="cuda")
+    jobs = []
+    for _ in range(n):
+        k, v = (torch.randint(0, 256, (B, H, cap, D // 4), generator=gen, device="cuda", dtype=torch.uint8) for _ in range(2))
+        jobs.append(dict(kn=rnd(B, H, D), vn=rnd(B, H, D), q=rnd(B, H * gqa, D), k=k, v=v,
+                         sc=torch.ones((B, H, cap), dtype=torch.bfloat16, device="cuda") if ks else None,
+                         out=torch.zeros((B, H * gqa, D), device="cuda"), stream=torch.cuda.Stream(),
+                         ws=torch.zeros(nk.decode_workspace_bytes(P, B, H * gqa, cap), dtype=torch.uint8, device="cuda")))
+
+    def step(j, stream=None):
+        nk.append_decode_attn(P, lay, j["kn"], j["vn"], j["q"], j["k"], j["v"], lens, cap, out=j["out"], workspace=j["ws"],
+                              k_scales=j["sc"], stream=stream)
+
+    print(f"[gpu-case] steps on {n} streams D={D} {fmt}", flush=True)
+    want = []
+    for j in jobs:
+        step(j)
+        torch.cuda.synchronize()
+        want.append([x.clone() for x in (j["out"], j["k"], j["v"])])
+    for _ in range(8):
+        for j in jobs:
+            j["out"].zero_()
+        torch.cuda.synchronize()
+        for j in jobs:
+            step(j, j["stream"])
+        torch.cuda.synchronize()
+        for j, w in zip(jobs, want):
+            close(j["out"], w[0], f"step on a stream D={D} {fmt}")
+            assert torch.equal(j["k"], w[1]) and torch.equal(j["v"], w[2])
